@@ -289,7 +289,7 @@ int check_host_workspace(void *host_ws, size_t bytes, size_t need, void **dev_pt
 
 // Scalar bounds of the device-built plan for a batch without host mirrors.
 struct DevLayout {
-    int32_t split_keys = 0, tile_tokens = 0, slots_per_desc = 0, head_chunks = 1,
+    int32_t split_blocks = 0, min_split = 0, max_split = 0, wave_slots = 0, tile_tokens = 0, slots_per_desc = 0, head_chunks = 1,
             heads_per_chunk = 1, waves_per_desc = 1, pf_max_blocks = 0;
     int64_t cap_desc = 0, cap_pdesc = 0, cap_mrows = 0, cap_ent = 0, cap_slots = 0;
     int64_t off_row_info = 0, off_desc = 0, off_pdesc = 0, off_mtok = 0, off_mptr = 0,
@@ -308,18 +308,22 @@ int dev_layout(const echo_kv_pool_t *pool, const echo_batch_t *b, int32_t Hq, De
     // longest length the scalars allow
     const PlanOptions o = plan_options(pool);
     const int64_t seg_blocks = B * (((int64_t)b->max_seq_len + kBlock - 1) / kBlock);
-    const int64_t split = std::max<int64_t>(
-        std::min(kMinSplitBlocks, std::max(2, o.split_blocks)),
+    L.min_split = std::min(kMinSplitBlocks, std::max(2, o.split_blocks));
+    L.split_blocks = (int32_t)std::max<int64_t>(
+        L.min_split,
         std::min<int64_t>(o.split_blocks, seg_blocks * Hkv * L.head_chunks / kSplitTargetUnits));
-    L.split_keys = (int32_t)(split * kBlock);
+    L.max_split = kOneGenerationStretch * o.split_blocks;
+    L.wave_slots = kDecodeWavesPerCu * o.num_cus;
+    const int64_t split_keys = (int64_t)L.split_blocks * kBlock;
     L.tile_tokens = (int32_t)std::max<int64_t>(1, kPrefillQueries / G);
-    const int64_t P = ((int64_t)b->max_seq_len + L.split_keys - 1) / L.split_keys;
+    const int64_t P = ((int64_t)b->max_seq_len + split_keys - 1) / split_keys;
     L.cap_desc = B * P;
     L.cap_ent = B * P;
     L.cap_mrows = B;
     L.cap_slots = B * P * L.slots_per_desc;
     L.cap_pdesc = std::min(B * (((int64_t)b->max_q_len + L.tile_tokens - 1) / L.tile_tokens),
                            ((int64_t)b->num_tokens + L.tile_tokens - 1) / L.tile_tokens + B);
+    if (b->max_q_len == 1) L.cap_pdesc = 0;   // rows of one token are decode work
     if (L.cap_desc * L.waves_per_desc > ((int64_t)1 << 31) - (1 << 20) ||
         L.cap_pdesc * Hkv > ((int64_t)1 << 31) - (1 << 20) || L.cap_slots > ((int64_t)1 << 31) - 1)
         return fail(ECHO_E_UNSUPPORTED, "batch too large for a plan built on the device");
@@ -491,15 +495,16 @@ int attn_device_planned(const echo_kv_pool_t *pool, const echo_batch_t *batch, c
     d.max_blocks_per_row = batch->max_blocks_per_row;
     d.num_blocks = pool->num_blocks;
     d.max_seq_len = batch->max_seq_len;
-    d.split_keys = L.split_keys;
+    d.split_blocks = L.split_blocks;
+    d.min_split_blocks = L.min_split;
+    d.max_split_blocks = L.max_split;
+    d.wave_slots = L.wave_slots;
+    d.waves_per_desc = L.waves_per_desc;
     d.tile_tokens = L.tile_tokens;
     d.slots_per_desc = L.slots_per_desc;
     d.prefill_max_keys = prefill_max_blocks(pool->head_dim) * kBlock;
     d.cap_desc = L.cap_desc;
     d.cap_pdesc = L.cap_pdesc;
-    d.cap_merge_rows = L.cap_mrows;
-    d.cap_ent = L.cap_ent;
-    d.cap_slots = L.cap_slots;
     d.row_info = w + L.off_row_info;
     d.hdr = w;
     d.desc = (WorkDesc *)(w + L.off_desc);

@@ -1351,22 +1351,31 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeArgs a) {
 // ------------------------------------------------------- device-built plan
 //
 // For batches given without host mirrors: the plan is built on the GPU from
-// the row metadata, with no prefix grouping.  Two kernels:
-//   dev_rows_kernel  one workgroup per row: checks the row's metadata and
-//                    block ids and records how many decode pieces or
-//                    prefill tiles it needs (-1: skipped)
-//   dev_plan_kernel  one workgroup: scans those counts and writes the
-//                    descriptors, merge lists and the header
-// Rows whose metadata is inconsistent (or that would not fit a region, which
-// only inconsistent q_start can cause) get no work and are counted in the
-// header, so every kernel after them stays inside its buffers.
+// the row metadata, with no prefix grouping.  A row is checked (its metadata
+// and block ids) before it gets work; rows whose metadata is inconsistent, or
+// whose tiles would not fit the prefill region (which only an inconsistent
+// q_start can cause), get none and are counted in the header, so every kernel
+// after the plan stays inside its buffers.  A row of one new token is decode
+// work whatever its kind: the same sum, without a prefill workgroup for it.
+//
+// What bounds it is latency: a handful of dependent loads, a scan and the
+// stores, for a few hundred descriptors.  So one workgroup does all of it when
+// it can check every block id in a few loads per thread, and the descriptors
+// are written flat, one per thread whatever row they belong to.  64 rows of up
+// to 4,096 keys: 9.6 us, where a check kernel and a thread per row that walked
+// its own pieces took 3.6 + 45 us beside 106 us of attention.
 
+__device__ __forceinline__ bool dev_row_ok(const DevPlanArgs &a, int t0, int t1, int L, int kind) {
+    const int q = t1 - t0;
+    return q >= 1 && L >= q && L <= a.max_seq_len && t0 >= 0 && t1 <= a.num_tokens &&
+           (kind == 0 ? q == 1 : kind == 1) && (kind == 0 || L <= a.prefill_max_keys);
+}
+
+// One workgroup per row: row_info[r] = 0, or -1 when the row is inconsistent.
 __global__ __launch_bounds__(256) void dev_rows_kernel(DevPlanArgs a) {
     const int r = blockIdx.x;
-    const int t0 = a.q_start[r], t1 = a.q_start[r + 1];
-    const int q = t1 - t0, L = a.seq_lens[r], kind = a.row_kind[r];
-    bool ok = q >= 1 && L >= q && L <= a.max_seq_len && t0 >= 0 && t1 <= a.num_tokens &&
-              (kind == 0 ? q == 1 : kind == 1) && (kind == 0 || L <= a.prefill_max_keys);
+    const int L = a.seq_lens[r];
+    const bool ok = dev_row_ok(a, a.q_start[r], a.q_start[r + 1], L, a.row_kind[r]);
     const int nb = ok ? (L + 15) / 16 : 0;
     const int32_t *bt = a.block_tables + (int64_t)r * a.max_blocks_per_row;
     int bad = 0;
@@ -1375,136 +1384,286 @@ __global__ __launch_bounds__(256) void dev_rows_kernel(DevPlanArgs a) {
         bad |= (id < 0 || id >= a.num_blocks);
     }
     bad = __syncthreads_or(bad);
-    if (threadIdx.x == 0) {
-        int n = -1;
-        if (ok && !bad)
-            n = kind == 0 ? (L + a.split_keys - 1) / a.split_keys : (q + a.tile_tokens - 1) / a.tile_tokens;
-        a.row_info[r] = n;
-    }
+    if (threadIdx.x == 0) a.row_info[r] = ok && !bad ? 0 : -1;
 }
 
-// exclusive scan over the 1024 threads of one workgroup of NV values per
-// thread; returns the totals in tot[]
-template <int NV>
-__device__ __forceinline__ void scan1024(int64_t (&v)[NV], int64_t (&tot)[NV], int64_t (*wsum)[NV]) {
+constexpr int kPlanThreads = 1024;   // rows per window of dev_plan_kernel
+constexpr int kPlanWaves = kPlanThreads / 64;
+
+// What a row adds to the plan: decode pieces, merged rows, merge entries,
+// prefill tiles.
+struct PlanCount {
+    int32_t dec, rows, ent;
+    int64_t pf;
+};
+
+// Exclusive scan of v over the workgroup's threads, of which only the first
+// `live` waves hold anything; tot receives the sum.
+__device__ __forceinline__ PlanCount plan_scan(const PlanCount &v, int live, PlanCount *wsum,
+                                               PlanCount &tot) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int64_t inc[NV];
+    PlanCount inc = v;
 #pragma unroll
-    for (int k = 0; k < NV; ++k) inc[k] = v[k];
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1)
-#pragma unroll
-        for (int k = 0; k < NV; ++k) {
-            const int64_t y = __shfl_up(inc[k], off);
-            if (lane >= off) inc[k] += y;
+    for (int off = 1; off < 64; off <<= 1) {
+        const int32_t d = __shfl_up(inc.dec, off), r = __shfl_up(inc.rows, off),
+                      e = __shfl_up(inc.ent, off);
+        const int64_t p = __shfl_up(inc.pf, off);
+        if (lane >= off) {
+            inc.dec += d;
+            inc.rows += r;
+            inc.ent += e;
+            inc.pf += p;
         }
-    if (lane == 63)
-#pragma unroll
-        for (int k = 0; k < NV; ++k) wsum[wave][k] = inc[k];
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < NV; ++k) {
-        int64_t before = 0, all = 0;
-        for (int w = 0; w < 16; ++w) {
-            before += w < wave ? wsum[w][k] : 0;
-            all += wsum[w][k];
-        }
-        v[k] = before + inc[k] - v[k];
-        tot[k] = all;
     }
-    __syncthreads();   // wsum is reused by the next call
+    if (lane == 63) wsum[wave] = inc;
+    __syncthreads();
+    PlanCount out = {inc.dec - v.dec, inc.rows - v.rows, inc.ent - v.ent, inc.pf - v.pf};
+    tot = {0, 0, 0, 0};
+    for (int w = 0; w < live; ++w) {
+        const PlanCount x = wsum[w];
+        if (w < wave) {
+            out.dec += x.dec;
+            out.rows += x.rows;
+            out.ent += x.ent;
+            out.pf += x.pf;
+        }
+        tot.dec += x.dec;
+        tot.rows += x.rows;
+        tot.ent += x.ent;
+        tot.pf += x.pf;
+    }
+    return out;
 }
 
-__global__ __launch_bounds__(1024) void dev_plan_kernel(DevPlanArgs a) {
-    __shared__ int64_t wsum[16][5];
-    __shared__ unsigned long long used[5];   // end of the written part of each region
-    __shared__ int bad_rows;
-    if (threadIdx.x < 5) used[threadIdx.x] = 0;
-    if (threadIdx.x == 0) bad_rows = 0;
-    __syncthreads();
-    const int64_t cap[5] = {a.cap_desc, a.cap_pdesc, a.cap_merge_rows, a.cap_ent, a.cap_slots};
-    int64_t carry[5] = {0, 0, 0, 0, 0};
-    for (int base = 0; base < a.num_rows; base += 1024) {
-        const int r = base + (int)threadIdx.x;
-        int info = -2, kind = 0;
-        if (r < a.num_rows) {
-            info = a.row_info[r];
-            kind = a.row_kind[r];
-        }
-        const int dec = (info > 0 && kind == 0) ? info : 0;
-        const int pf = (info > 0 && kind == 1) ? info : 0;
-        // counts: decode pieces, prefill tiles, merged tokens, merge entries, slots
-        int64_t v[5] = {dec, pf, dec > 1 ? 1 : 0, dec > 1 ? dec : 0,
-                        dec > 1 ? (int64_t)dec * a.slots_per_desc : 0};
-        const int64_t n[5] = {v[0], v[1], v[2], v[3], v[4]};
-        int64_t tot[5];
-        scan1024<5>(v, tot, wsum);
-        int64_t off[5];
-        bool fits = true;
+// last i in [0, n) with off[i] <= x (off ascending, off[0] <= x)
+__device__ __forceinline__ int plan_find(const int32_t *off, int n, int x) {
+    int lo = 0, hi = n - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (off[mid] <= x) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+
+// CHECK: a launch of one workgroup that checks the block ids as well (at most
+// kPlanThreads rows); otherwise dev_rows_kernel has, every workgroup scans all
+// rows, and the workgroups share the writing.
+template <bool CHECK>
+__global__ __launch_bounds__(kPlanThreads) void dev_plan_kernel(DevPlanArgs a) {
+    __shared__ int32_t row_dec[kPlanThreads], row_pf[kPlanThreads];      // first descriptor
+    __shared__ int32_t row_np[kPlanThreads], row_ent[kPlanThreads];      // pieces, first entry
+    __shared__ int32_t row_len[kPlanThreads], row_t0[kPlanThreads], row_q[kPlanThreads];
+    __shared__ PlanCount wsum[kPlanWaves];
+    __shared__ int64_t wsum_l[kPlanWaves];
+    __shared__ int bad_rows, used_pf;
+    const int tid = threadIdx.x;
+    const int B = a.num_rows;
+    if (tid == 0) bad_rows = used_pf = 0;
+
+    int t0 = 0, q = 0, L = 0;
+    bool ok = false;
+    auto load_row = [&](int r) {
+        t0 = q = L = 0;
+        ok = false;
+        if (r >= B) return;
+        t0 = a.q_start[r];
+        const int t1 = a.q_start[r + 1];
+        L = a.seq_lens[r];
+        ok = CHECK ? dev_row_ok(a, t0, t1, L, a.row_kind[r]) : a.row_info[r] == 0;
+        q = t1 - t0;
+    };
+    if constexpr (CHECK) {
+        // every (row, block) of the table's used width, eight loads in flight,
+        // the first ones beside the row metadata (entries past a row's end are
+        // read and not looked at)
+        constexpr int N = 8;
+        const int W = (a.max_seq_len + 15) / 16;
+        const int n = B * W;
+        const int dr = kPlanThreads / W, dj = kPlanThreads - dr * W;
+        int row = tid / W, j = tid - row * W;   // of the next entry to load
+        int id[N], er[N], ej[N];
+        auto load = [&](int base) {
 #pragma unroll
-        for (int k = 0; k < 5; ++k) {
-            off[k] = carry[k] + v[k];
-            fits = fits && off[k] + n[k] <= cap[k];
-            carry[k] += tot[k];
-        }
-        if (r < a.num_rows && (info == -1 || !fits)) atomicAdd(&bad_rows, 1);
-        if (r < a.num_rows && fits && (dec > 0 || pf > 0)) {
-#pragma unroll
-            for (int k = 0; k < 5; ++k)
-                if (n[k] > 0) atomicMax(&used[k], (unsigned long long)(off[k] + n[k]));
-            const int t0 = a.q_start[r];
-            const int L = a.seq_lens[r];
-            for (int p = 0; p < dec; ++p) {
-                WorkDesc d;
-                d.tok_off = 0;
-                d.shape = 1;
-                d.bt_row = r;
-                d.key_begin = p * a.split_keys;
-                d.key_end = min((p + 1) * a.split_keys, L);
-                d.part = dec > 1 ? (int32_t)(off[4] + (int64_t)p * a.slots_per_desc) : -1;
-                d.tok1 = t0;
-                d.klim1 = L;
-                a.desc[off[0] + p] = d;
-            }
-            if (dec > 1) {
-                a.merge_tok[off[2]] = t0;
-                a.merge_ptr[off[2]] = (int32_t)off[3];
-                for (int p = 0; p < dec; ++p) {
-                    a.merge_ent[2 * (off[3] + p)] = (int32_t)(off[4] + (int64_t)p * a.slots_per_desc);
-                    a.merge_ent[2 * (off[3] + p) + 1] = 1;   // a one-token slice, query 0
+            for (int k = 0; k < N; ++k) {
+                er[k] = row;
+                ej[k] = base + k * kPlanThreads + tid < n ? j : W;
+                id[k] = ej[k] < W ? a.block_tables[(int64_t)row * a.max_blocks_per_row + j] : 0;
+                row += dr;
+                j += dj;
+                if (j >= W) {
+                    j -= W;
+                    ++row;
                 }
             }
-            const int q = a.q_start[r + 1] - t0, c = L - q;
-            for (int k = 0; k < pf; ++k) {   // the tile with the most keys first
-                const int kk = pf - 1 - k;
-                PrefillDesc d;
-                d.row = r;
-                d.tok0 = t0 + kk * a.tile_tokens;
-                d.ntok = min(a.tile_tokens, q - kk * a.tile_tokens);
-                d.key_end = c + kk * a.tile_tokens + d.ntok;
-                d.key_begin = 0;
-                d.part = -1;
-                d.kfull = d.key_end - d.ntok + 1;
-                d.next = 0;
-                a.pdesc[off[1] + k] = d;
-            }
+        };
+        load(0);
+        load_row(tid);
+        row_np[tid] = ok ? (L + 15) / 16 : 0;
+        row_ent[tid] = 0;   // set by a bad block id
+        __syncthreads();
+        for (int base = 0; base < n; base += N * kPlanThreads) {
+            if (base > 0) load(base);
+#pragma unroll
+            for (int k = 0; k < N; ++k)
+                if ((uint32_t)id[k] >= (uint32_t)a.num_blocks && ej[k] < W && ej[k] < row_np[er[k]])
+                    row_ent[er[k]] = 1;
+        }
+        __syncthreads();
+        ok = ok && !row_ent[tid];
+        __syncthreads();
+    }
+
+    // Pieces of decode rows: the host planner's rule (build_plan) on the blocks
+    // there are, but no shorter than the descriptor region allows.  The region
+    // holds every row cut into pieces of split_blocks, the rule's value for
+    // the longest lengths the scalars allow.
+    auto dec_blocks = [&]() -> int { return ok && q == 1 ? (L + 15) / 16 : 0; };
+    int64_t blocks = 0;
+    {
+        int64_t mine = 0;
+        for (int base = 0; base < B; base += kPlanThreads) {
+            if constexpr (!CHECK) load_row(base + tid);
+            mine += dec_blocks();
+        }
+        row_np[tid] = (int32_t)mine;   // a row's own blocks when one window holds them all
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) mine += __shfl_xor(mine, off);
+        if ((tid & 63) == 0) wsum_l[tid >> 6] = mine;
+        __syncthreads();
+        for (int w = 0; w < kPlanWaves; ++w) blocks += wsum_l[w];
+        __syncthreads();   // wsum_l is rewritten
+    }
+    const int64_t units_cap = min<int64_t>(blocks * a.waves_per_desc / kSplitTargetUnits,
+                                           a.max_split_blocks);
+    const uint32_t room = (uint32_t)(a.cap_desc - B);   // 0: the region holds one piece per row
+    int lo = a.split_blocks;                            // shortest piece that fits the region
+    if (room > 0 && blocks < ((int64_t)1 << 31))
+        lo = min(lo, max(a.min_split_blocks, (int)(((uint32_t)blocks + room - 1) / room)));
+    int split = min(a.split_blocks, max(lo, (int)units_cap));
+    if (B <= kPlanThreads) {
+        // each wave counts the pieces of one candidate length; two rounds of
+        // kPlanWaves candidates narrow the shortest one whose launch fits the chip
+        int hi = max(split, (int)units_cap);
+        for (int round = 0; round < 2; ++round) {
+            const int step = (hi - lo + kPlanWaves - 2) / (kPlanWaves - 1);
+            const int cand = min(lo + (tid >> 6) * step, hi);
+            int n = 0;
+            for (int r = tid & 63; r < B; r += 64) n += (row_np[r] + cand - 1) / cand;
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) n += __shfl_xor(n, off);
+            if ((tid & 63) == 0) wsum_l[tid >> 6] = (int64_t)n * a.waves_per_desc;
+            __syncthreads();
+            int w = 0;
+            while (w < kPlanWaves - 1 && wsum_l[w] > a.wave_slots) ++w;
+            const bool fits = wsum_l[w] <= a.wave_slots;
+            __syncthreads();
+            if (!fits) break;   // several generations: the default length
+            split = min(lo + w * step, hi);
+            if (w == 0 || step <= 1) break;
+            hi = split;
+            lo = hi - step + 1;
         }
     }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        a.hdr[kHdrDesc] = (int32_t)used[0];
-        a.hdr[kHdrPdesc] = (int32_t)used[1];
-        a.hdr[kHdrMergeRows] = (int32_t)used[2];
-        a.hdr[kHdrSlots] = (int32_t)used[4];
+
+    int32_t done_dec = 0, done_rows = 0, done_ent = 0;
+    int64_t done_pf = 0;
+    for (int base = 0; base < B; base += kPlanThreads) {
+        const int nr = min(kPlanThreads, B - base);
+        const int live = (nr + 63) / 64;
+        if constexpr (!CHECK) load_row(base + tid);
+        const int nb = dec_blocks();
+        const int np = (nb + split - 1) / split;
+        const int tiles = ok && q > 1 ? (q + a.tile_tokens - 1) / a.tile_tokens : 0;
+        const bool merged = np > 1;
+        PlanCount tot;
+        const PlanCount at = plan_scan({np, merged ? 1 : 0, merged ? np : 0, tiles}, live, wsum, tot);
+        const bool fits = done_pf + at.pf + tiles <= a.cap_pdesc;
+        row_dec[tid] = at.dec;
+        row_pf[tid] = (int32_t)min<int64_t>(at.pf, a.cap_pdesc - min<int64_t>(done_pf, a.cap_pdesc));
+        row_np[tid] = np;
+        row_ent[tid] = merged ? done_ent + at.ent : -1;
+        row_len[tid] = L;
+        row_t0[tid] = t0;
+        row_q[tid] = q;
+        if (base + tid < B && (!ok || !fits)) atomicAdd(&bad_rows, 1);
+        if (tiles > 0 && fits) atomicMax(&used_pf, (int)(done_pf + at.pf + tiles));
+        if (merged && blockIdx.x == 0) {
+            a.merge_tok[done_rows + at.rows] = t0;
+            a.merge_ptr[done_rows + at.rows] = done_ent + at.ent;
+        }
+        __syncthreads();
+        for (int i = blockIdx.x * kPlanThreads + tid; i < tot.dec; i += gridDim.x * kPlanThreads) {
+            const int k = plan_find(row_dec, nr, i);
+            const int p = i - row_dec[k], pieces = row_np[k], len = row_len[k];
+            const int step = 16 * (((len + 15) / 16 + pieces - 1) / pieces);   // equal pieces
+            const int ent = row_ent[k];
+            const int slot = ent < 0 ? -1 : (ent + p) * a.slots_per_desc;
+            WorkDesc d;
+            d.tok_off = 0;
+            d.shape = 1;
+            d.bt_row = base + k;
+            d.key_begin = p * step;
+            d.key_end = min((p + 1) * step, len);
+            d.part = slot;
+            d.tok1 = row_t0[k];
+            d.klim1 = len;
+            a.desc[done_dec + i] = d;
+            if (ent >= 0) {
+                a.merge_ent[2 * (int64_t)(ent + p)] = slot;
+                a.merge_ent[2 * (int64_t)(ent + p) + 1] = 1;   // a one-token slice, query 0
+            }
+        }
+        // the tiles this window may write: those of the rows that fit
+        const int64_t room_pf = max<int64_t>(0, used_pf - done_pf);
+        const int n_tiles = (int)min<int64_t>(tot.pf, room_pf);
+        for (int i = blockIdx.x * kPlanThreads + tid; i < n_tiles; i += gridDim.x * kPlanThreads) {
+            const int k = plan_find(row_pf, nr, i);
+            const int qk = row_q[k], c = row_len[k] - qk;
+            const int n = (qk + a.tile_tokens - 1) / a.tile_tokens;
+            const int first = (n - 1 - (i - row_pf[k])) * a.tile_tokens;   // most keys first
+            PrefillDesc d;
+            d.row = base + k;
+            d.tok0 = row_t0[k] + first;
+            d.ntok = min(a.tile_tokens, qk - first);
+            d.key_end = c + first + d.ntok;
+            d.key_begin = 0;
+            d.part = -1;
+            d.kfull = d.key_end - d.ntok + 1;
+            d.next = 0;
+            a.pdesc[done_pf + i] = d;
+        }
+        done_dec += tot.dec;
+        done_rows += tot.rows;
+        done_ent += tot.ent;
+        done_pf += tot.pf;
+        __syncthreads();   // the window's arrays are rewritten
+    }
+    if (tid == 0 && blockIdx.x == 0) {
+        a.hdr[kHdrDesc] = done_dec;
+        a.hdr[kHdrPdesc] = used_pf;
+        a.hdr[kHdrMergeRows] = done_rows;
+        a.hdr[kHdrSlots] = done_ent * a.slots_per_desc;
         a.hdr[kHdrBadRows] = bad_rows;
-        a.merge_ptr[used[2]] = (int32_t)used[3];
+        a.merge_ptr[done_rows] = done_ent;
     }
 }
+
+// Block ids that one workgroup checks by itself: 32 loads per thread, which
+// cost less than a launch of a workgroup per row before it (3.7 us and a gap).
+constexpr int64_t kPlanCheckIds = 32 * kPlanThreads;
 
 hipError_t launch_dev_plan(const DevPlanArgs &a, hipStream_t s) {
     if (a.num_rows <= 0) return hipSuccess;
+    const int64_t width = ((int64_t)a.max_seq_len + 15) / 16;
+    if (a.num_rows <= kPlanThreads && a.num_rows * width <= kPlanCheckIds) {
+        hipLaunchKernelGGL((dev_plan_kernel<true>), dim3(1), dim3(kPlanThreads), 0, s, a);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(dev_rows_kernel, dim3((unsigned)a.num_rows), dim3(256), 0, s, a);
-    hipLaunchKernelGGL(dev_plan_kernel, dim3(1), dim3(1024), 0, s, a);
+    // every workgroup repeats the scan, so only as many as the writing fills
+    const int64_t wg = std::min<int64_t>(64, 1 + (a.cap_desc + a.cap_pdesc) / (4 * kPlanThreads));
+    hipLaunchKernelGGL((dev_plan_kernel<false>), dim3((unsigned)wg), dim3(kPlanThreads), 0, s, a);
     return hipGetLastError();
 }
 

@@ -78,20 +78,24 @@ struct MergeArgs {
 };
 
 // The plan of a batch without host mirrors, built on the device into the
-// workspace: no prefix grouping; decode rows cut into pieces of split_keys,
-// prefill rows into tiles of tile_tokens tokens.  Regions have capacities
+// workspace: no prefix grouping; decode rows cut into pieces of at most
+// split_blocks blocks, prefill rows into tiles of tile_tokens tokens.  Regions have capacities
 // from the host's scalar bounds; the header holds the counts the attention
 // kernels read (DevPlanHeader).
 struct DevPlanArgs {
     const int32_t *block_tables, *seq_lens, *q_start;
     const uint8_t *row_kind;
     int32_t num_rows, num_tokens, max_blocks_per_row, num_blocks, max_seq_len;
-    int32_t split_keys;             // keys per decode piece (multiple of 16)
+    int32_t split_blocks;           // decode piece of the descriptor region's bound
+    int32_t min_split_blocks, max_split_blocks;   // shortest and longest piece of the rule
+    int32_t wave_slots;             // decode waves the chip keeps resident
+    int32_t waves_per_desc;         // num_kv_heads * head_chunks
     int32_t tile_tokens;            // tokens per prefill tile
     int32_t slots_per_desc;         // partial slots per decode piece (one token)
     int32_t prefill_max_keys;       // longest key range the prefill kernel can stage
-    int64_t cap_desc, cap_pdesc, cap_merge_rows, cap_ent, cap_slots;
-    int32_t *row_info;              // [num_rows] scratch: decode pieces | prefill tiles << 16, or -1
+    int64_t cap_desc, cap_pdesc;    // region sizes; every row cut into pieces of split_blocks
+                                    // fits cap_desc, and so do its merge entries and slots
+    int32_t *row_info;              // [num_rows] scratch: 0, or -1 for an inconsistent row
     int32_t *hdr;                   // DevPlanHeader words
     WorkDesc *desc;
     PrefillDesc *pdesc;

@@ -146,14 +146,16 @@ int build_plan(const HostBatch &b, int32_t Hkv, int32_t Hq, int32_t D, const Pla
         return n * plan.waves_per_desc;
     };
     // A launch that fits one generation of resident waves starts every wave
-    // at once and has no partly filled last generation: when pieces up to
-    // kOneGenerationStretch times longer (and no longer than the unit target
-    // allows) bring the launch under that, take the shortest such length.
+    // at once and has no partly filled last generation: take the shortest
+    // pieces, from kMinSplitBlocks up to kOneGenerationStretch times the
+    // default (and no longer than the unit target allows), that bring the
+    // launch under that.  Short of it the launch leaves slots empty, and a CU
+    // that holds three workgroups beside CUs that hold two ends the kernel.
     const int64_t slots = (int64_t)kDecodeWavesPerCu * opt.num_cus;
-    const int32_t stretch_cap = (int32_t)std::max<int64_t>(
+    const int32_t longest = (int32_t)std::max<int64_t>(
         split, std::min<int64_t>((int64_t)kOneGenerationStretch * opt.split_blocks, units_cap));
-    if (waves_for(split) > slots && waves_for(stretch_cap) <= slots) {
-        int32_t lo = split + 1, hi = stretch_cap;
+    if (waves_for(longest) <= slots) {
+        int32_t lo = min_split, hi = longest;
         while (lo < hi) {
             const int32_t mid = lo + (hi - lo) / 2;
             if (waves_for(mid) <= slots) hi = mid;

@@ -69,7 +69,10 @@ constexpr int kPrefillMinChainTiles = 2;  // fewest 64-key tiles moved to a chai
 // the bytes per block (a sweep of 16-128 blocks on the decode-only, mixed and
 // e4m3 batches).
 constexpr int64_t kSplitBytes = 384 * 1024;
-constexpr int kMinSplitBlocks = 8;        // shortest decode piece on small batches
+#ifndef ECHO_MIN_SPLIT
+#define ECHO_MIN_SPLIT 8
+#endif
+constexpr int kMinSplitBlocks = ECHO_MIN_SPLIT;        // shortest decode piece on small batches
 constexpr int kSplitTargetUnits = 2048;   // decode units below which pieces shrink
 #ifndef ECHO_EQ_GENS
 #define ECHO_EQ_GENS 3
