@@ -54,20 +54,15 @@ __device__ __forceinline__ bf16x8_t e4m3x8_to_bf16x8(u32x2_t w) {
     return (bf16x8_t){a[0], a[1], b[0], b[1], c[0], c[1], d[0], d[1]};
 }
 
-// fp32 -> OCP e4m3fn, round to nearest even, saturating to +-448, NaN to
-// 0x7F; without branches, so that the lanes of a wave do not diverge over
-// the value ranges.  Normal range (|y| >= 2^-6): round the bit pattern to 3
-// mantissa bits (a carry moves into the exponent), then rebias the exponent
-// (127 -> 7: minus 120 << 3); below it, steps of 2^-9 (|y| * 512 is exact).
-__device__ __forceinline__ uint32_t f32_to_e4m3(float y) {
-    const uint32_t u = __float_as_uint(y);
-    const uint32_t sign = (u >> 24) & 0x80u;
-    const uint32_t a = u & 0x7FFFFFFFu;
-    const uint32_t a_sat = a < 0x43E00000u ? a : 0x43E00000u;            // |y| >= 448, inf -> 448
-    const uint32_t cn = ((a_sat + 0x7FFFFu + ((a_sat >> 20) & 1u)) >> 20) - 960u;
-    const uint32_t cs = (uint32_t)__builtin_rintf(__uint_as_float(a) * 512.0f);
-    const uint32_t code = sign | (a < 0x3C800000u ? cs : (cn < 0x7Eu ? cn : 0x7Eu));
-    return a > 0x7F800000u ? 0x7Fu : code;
+// Two fp32 -> two OCP e4m3fn codes in the low 16 bits, round to nearest even,
+// saturating to +-448, NaN to 0x7F: gfx950's v_cvt_pk_fp8_f32 on the clamped
+// values (checked on all 2^32 floats against an integer encoder).
+__device__ __forceinline__ uint32_t f32x2_to_e4m3(float x, float y) {
+    const uint32_t w = (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(
+        __builtin_amdgcn_fmed3f(x, -448.f, 448.f), __builtin_amdgcn_fmed3f(y, -448.f, 448.f), 0, false);
+    const uint32_t nan = (x != x ? 0x7Fu : 0u) | (y != y ? 0x7F00u : 0u);
+    const uint32_t keep = (x != x ? 0u : 0xFFu) | (y != y ? 0u : 0xFF00u);
+    return (w & keep) | nan;
 }
 
 // The quotient RN(x / s) that the quantisation takes, for a divisor s shared
@@ -78,15 +73,21 @@ __device__ __forceinline__ uint32_t f32_to_e4m3(float y) {
 // x (checked exhaustively on the CPU over x and every scale fp32(b / 448), b
 // a positive bf16); quotients past 512 saturate either way and keep q0, and
 // the sign is q0's (a zero x keeps its sign).  Other scales divide.
+// The scale is the wave's, so it is kept scalar and the choice is one branch.
 struct Recip {
     float s, r;
     bool fast;
 };
-__device__ __forceinline__ Recip recip_of(float s) {
-    return {s, 1.0f / s, s >= 0x1p-100f && s <= 0x1p100f};
+__device__ __forceinline__ float uniform(float x) {
+    return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(x)));
 }
+__device__ __forceinline__ Recip recip_of(float s) {
+    s = uniform(s);
+    return {s, uniform(1.0f / s), s >= 0x1p-100f && s <= 0x1p100f};
+}
+template <bool FAST>
 __device__ __forceinline__ float quotient(float x, const Recip &d) {
-    if (!d.fast) return x / d.s;
+    if constexpr (!FAST) return x / d.s;
     const float q0 = x * d.r;
     const float e = __builtin_fmaf(-q0, d.s, x);
     const float q1 = __builtin_fmaf(e, d.r, q0);
@@ -115,143 +116,124 @@ __device__ __forceinline__ float wave_max_xor16_32(float x) {
 
 // ------------------------------------------------------------------- append
 
-// One work unit = (row, written block, KV head).  Units are enumerated
-// without host help: every workgroup scans the rows' written-block counts
-// into LDS (windows of kAppWin rows), then each wave takes every n-th unit of
-// the window and finds its row by binary search over the prefix.
-constexpr int kAppWin = 2048;
+// One work unit = (row, written block, KV head), one wave each.  Bound by
+// memory latency and by how the accesses coalesce, so a block goes through the
+// wave in 16-byte pieces both ways: lane (a, c) holds the 16-byte chunk c of
+// slots SL * a .. + SL (SL = D / 32), so that every load and every K store of
+// the wave covers whole rows; V's SL slots x 8 values are transposed in
+// registers, and the wave's LDS tile turns them into whole 1 KiB runs of the
+// [d][16 slots] tile.  A block written in part (a decode row's slot, a chunk's
+// ends) reads its V tile beside the new tokens and writes it back whole: the
+// L2 would fetch those lines for 2-byte stores as well.  9,924 prompt tokens
+// (8 KV heads, head_dim 64, bf16): 27 -> 10 us, 4 TB/s; 16,412 tokens at
+// head_dim 128: 35 -> 27 us, 5 TB/s; 4,640 tokens of 546 rows into an e4m3
+// cache: 28.7 -> 16.7 us; 256 decode rows of 32 heads: 17.2 -> 15.6 us.
 
-// exclusive prefix of cnt[0..n) in place (n <= kAppWin); returns the total
-__device__ __forceinline__ int block_scan_window(int32_t *cnt, int n, int32_t *wsum) {
-    constexpr int PER = kAppWin / 256;
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    int loc = 0;
+// Codes of eight bf16 values, in order
+template <bool FAST>
+__device__ __forceinline__ u32x2_t e4m3x8_by(const u32x4_t &w, const Recip &d) {
+    u32x2_t c;
 #pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        const int i = t * PER + k;
-        loc += i < n ? cnt[i] : 0;
-    }
-    int inc = loc;  // inclusive scan over the wave
+    for (int x = 0; x < 2; ++x) {
+        uint32_t h[2];
 #pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int y = __shfl_up(inc, off);
-        if (lane >= off) inc += y;
-    }
-    if (lane == 63) wsum[wave] = inc;
-    __syncthreads();
-    int before = 0, total = 0;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-        before += w < wave ? wsum[w] : 0;
-        total += wsum[w];
-    }
-    int run = before + inc - loc;
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        const int i = t * PER + k;
-        if (i < n) {
-            const int c = cnt[i];
-            cnt[i] = run;
-            run += c;
+        for (int y = 0; y < 2; ++y) {
+            const uint32_t v = w[2 * x + y];
+            h[y] = f32x2_to_e4m3(quotient<FAST>(bf16_bits_to_f32(v & 0xFFFFu), d),
+                                 quotient<FAST>(bf16_bits_to_f32(v >> 16), d));
         }
+        c[x] = h[0] | (h[1] << 16);
     }
-    __syncthreads();
-    return total;
+    return c;
+}
+__device__ __forceinline__ u32x2_t e4m3x8(const u32x4_t &w, const Recip &d) {
+    return d.fast ? e4m3x8_by<true>(w, d) : e4m3x8_by<false>(w, d);
 }
 
-// Lane (m, part) = (lane / 4, lane % 4) carries slot m's token: the quarter
-// `part` of its K and V rows (D / 4 values).  Slot m holds position 16j + m
-// and is written when m_lo <= m < m_hi.  K rows go straight to the pool;
-// V rows are transposed through the wave's LDS tile to [d][16 slots] and
-// written as whole 16-slot rows when the block is full, else slot by slot.
-// e4m3: a block that is not written whole (a decode row's slot) quantises
-// only its written slots, each slot's K and V rows spread over all 64 lanes.
+// byte i of the result: byte (sel >> 8i & 7) of the pair (hi: 4..7, lo: 0..3)
+__device__ __forceinline__ uint32_t bytes(uint32_t hi, uint32_t lo, uint32_t sel) {
+    return __builtin_amdgcn_perm(hi, lo, sel);
+}
+
+__device__ __forceinline__ float absmax8(const u32x4_t &w, float m) {
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+        m = fmaxf(m, fmaxf(fabsf(bf16_bits_to_f32(w[x] & 0xFFFFu)), fabsf(bf16_bits_to_f32(w[x] >> 16))));
+    return m;
+}
+
+__device__ __forceinline__ float wave_max(float m) {
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
+    return m;
+}
+
+// LDS of one wave's V tile: rows d of 16 slots, 8 rows and a pad per chunk
+// (the pad spreads the chunks over the banks)
 template <int D, bool FP8>
-__device__ __forceinline__ void append_unit(const AppendArgs &a, int r, int j, int h, int lane,
-                                            uint16_t *tr, int t0, int p0, int L) {
-    if (j >= a.max_blocks_per_row) return;
-    const int blk = a.block_tables[(int64_t)r * a.max_blocks_per_row + j];
-    if (blk < 0 || blk >= a.num_blocks) return;
-    const int sb = 16 * j;
-    const int m_lo = max(p0, sb) - sb, m_hi = min(L, sb + 16) - sb;   // written slots
-    const bool full = m_lo == 0 && m_hi == 16;
-    const int m = lane >> 2, part = lane & 3;
-    const bool mine = m >= m_lo && m < m_hi;
-    constexpr int QW = D / 32;        // 16-byte words per quarter row
-    const int64_t tok_stride = (int64_t)a.num_kv_heads * D;
-    const int64_t row_src = (int64_t)(t0 + sb - p0 + m) * tok_stride + (int64_t)h * D + part * (D / 4);
-    const int64_t tile = ((int64_t)blk * a.num_kv_heads + h) * 16 * D;
+struct AppendTile {
+    static constexpr int ROW = FP8 ? 16 : 32;              // bytes
+    static constexpr int CHUNK = 8 * ROW + (FP8 ? 16 : 32);
+    static constexpr int BYTES = D / 8 * CHUNK;
+};
 
-    u32x4_t kw[QW], vw[QW];
+// Slots m0 .. m0 + n - 1 of block blk, head h, from tokens t .. t + n - 1.
+template <int D, bool FP8>
+__device__ __forceinline__ void append_block(const AppendArgs &a, int blk, int h, int64_t t, int m0,
+                                             int n, int lane, uint8_t *lds) {
+    typedef AppendTile<D, FP8> TL;
+    constexpr int SL = D / 32, CH = D / 8;   // slots per lane, 16-byte chunks per row
+    constexpr int NU = D * TL::ROW / 1024;   // 1 KiB runs of the V tile
+    const int c = lane % CH, s0 = SL * (lane / CH);
+    const int64_t H = a.num_kv_heads, src = (t + s0 - m0) * H * D + (int64_t)h * D + 8 * c;
+    const int64_t tile = ((int64_t)blk * H + h) * 16 * D;
+    const bool full = n == 16;
+    bool mine[SL];
+    u32x4_t kw[SL], vw[SL], old[NU];
 #pragma unroll
-    for (int w = 0; w < QW; ++w) {
+    for (int w = 0; w < SL; ++w) {
+        mine[w] = (uint32_t)(s0 + w - m0) < (uint32_t)n;
         kw[w] = vw[w] = (u32x4_t){0u, 0u, 0u, 0u};
-        if (mine) {
-            kw[w] = *(const u32x4_t *)(a.k_new + row_src + 8 * w);
-            vw[w] = *(const u32x4_t *)(a.v_new + row_src + 8 * w);
+        if (mine[w]) {
+            kw[w] = *(const u32x4_t *)(a.k_new + src + w * H * D);
+            vw[w] = *(const u32x4_t *)(a.v_new + src + w * H * D);
         }
     }
-    // stage V as [slot][D] bf16 in this wave's LDS tile, read back by d
-    if (mine) {
+    uint8_t *vdst = (uint8_t *)a.v + tile * (FP8 ? 1 : 2) + 16 * lane;
+    if (!full) {
 #pragma unroll
-        for (int w = 0; w < QW; ++w) *(u32x4_t *)(tr + m * D + part * (D / 4) + 8 * w) = vw[w];
+        for (int i = 0; i < NU; ++i) old[i] = *(const u32x4_t *)(vdst + i * 1024);
     }
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    constexpr int DPL = D / 64;       // d rows of V^T per lane
-    uint32_t col[16];                 // slot s of this lane's d rows (DPL bf16 each)
-#pragma unroll
-    for (int s2 = 0; s2 < 16; ++s2) {
-        if constexpr (DPL == 2) col[s2] = *(const uint32_t *)(tr + s2 * D + 2 * lane);
-        else col[s2] = tr[s2 * D + lane];
-    }
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-
+    uint8_t *vl = lds + c * TL::CHUNK + s0 * (FP8 ? 1 : 2);
     if constexpr (!FP8) {
-        uint16_t *kdst = (uint16_t *)a.k + tile;
-        uint16_t *vdst = (uint16_t *)a.v + tile;
-        if (mine) {
+        uint16_t *kdst = (uint16_t *)a.k + tile + s0 * D + 8 * c;
 #pragma unroll
-            for (int w = 0; w < QW; ++w) *(u32x4_t *)(kdst + m * D + part * (D / 4) + 8 * w) = kw[w];
-        }
+        for (int w = 0; w < SL; ++w)
+            if (mine[w]) *(u32x4_t *)(kdst + w * D) = kw[w];
 #pragma unroll
-        for (int e = 0; e < DPL; ++e) {
-            uint16_t *row = vdst + (lane * DPL + e) * 16;
-            if (full) {
-                uint32_t pk[8];
+        for (int x = 0; x < 4; ++x)
 #pragma unroll
-                for (int m2 = 0; m2 < 8; ++m2)
-                    pk[m2] = ((col[2 * m2] >> (16 * e)) & 0xFFFFu) |
-                             (((col[2 * m2 + 1] >> (16 * e)) & 0xFFFFu) << 16);
-                *(u32x4_t *)row = (u32x4_t){pk[0], pk[1], pk[2], pk[3]};
-                *(u32x4_t *)(row + 8) = (u32x4_t){pk[4], pk[5], pk[6], pk[7]};
-            } else {
-                // the written slots only: 2-byte stores at fixed offsets from the row
-#pragma unroll
-                for (int s2 = 0; s2 < 16; ++s2)
-                    if (s2 >= m_lo && s2 < m_hi) row[s2] = (uint16_t)(col[s2] >> (16 * e));
+            for (int e = 0; e < 2; ++e) {   // d = 8c + 2x + e
+                const uint32_t sel = e ? 0x07060302u : 0x05040100u;
+                uint8_t *row = vl + (2 * x + e) * TL::ROW;
+                if constexpr (SL == 4)
+                    *(u32x2_t *)row = (u32x2_t){bytes(vw[1][x], vw[0][x], sel),
+                                                bytes(vw[SL - 1][x], vw[SL - 2][x], sel)};
+                else
+                    *(uint32_t *)row = bytes(vw[1][x], vw[0][x], sel);
             }
-        }
     } else {
-        uint8_t *kdst = (uint8_t *)a.k + tile;
-        uint8_t *vdst = (uint8_t *)a.v + tile;
-        const int64_t si = (int64_t)blk * a.num_kv_heads + h;
+        const int64_t si = (int64_t)blk * H + h;
         float sk, sv;
-        if (m_lo == 0) {  // slot 0 written by this call: fresh scales
+        if (m0 == 0) {   // slot 0 written by this call: fresh scales
             float ak = 0.f, av = 0.f;
 #pragma unroll
-            for (int w = 0; w < QW; ++w)
-#pragma unroll
-                for (int x = 0; x < 4; ++x) {
-                    ak = fmaxf(ak, fmaxf(fabsf(bf16_bits_to_f32(kw[w][x] & 0xFFFFu)),
-                                         fabsf(bf16_bits_to_f32(kw[w][x] >> 16))));
-                    av = fmaxf(av, fmaxf(fabsf(bf16_bits_to_f32(vw[w][x] & 0xFFFFu)),
-                                         fabsf(bf16_bits_to_f32(vw[w][x] >> 16))));
-                }
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) {
-                ak = fmaxf(ak, __shfl_xor(ak, off));
-                av = fmaxf(av, __shfl_xor(av, off));
+            for (int w = 0; w < SL; ++w) {
+                ak = absmax8(kw[w], ak);
+                av = absmax8(vw[w], av);
             }
+            ak = wave_max(ak);
+            av = wave_max(av);
             sk = ak == 0.f ? 1.f : ak / 448.0f;
             sv = av == 0.f ? 1.f : av / 448.0f;
             if (lane == 0) {
@@ -263,192 +245,131 @@ __device__ __forceinline__ void append_unit(const AppendArgs &a, int r, int j, i
             sv = a.v_scale[si];
         }
         const Recip dk = recip_of(sk), dv = recip_of(sv);
-        if (!full) {
-            // the written slots only, each K row spread over the whole wave
-            // (DPL values per lane), as V below
+        uint8_t *kdst = (uint8_t *)a.k + tile + s0 * D + 8 * c;
+        u32x2_t vc[SL];
 #pragma unroll
-            for (int s2 = 0; s2 < 16; ++s2) {
-                if (s2 < m_lo || s2 >= m_hi) continue;
-                const uint16_t *kp = a.k_new + (int64_t)(t0 + sb - p0 + s2) * tok_stride +
-                                     (int64_t)h * D + lane * DPL;
-                const uint32_t w = DPL == 2 ? *(const uint32_t *)kp : (uint32_t)*kp;
-                uint32_t c = 0;
-#pragma unroll
-                for (int e = 0; e < DPL; ++e)
-                    c |= f32_to_e4m3(quotient(bf16_bits_to_f32((w >> (16 * e)) & 0xFFFFu), dk)) << (8 * e);
-                if constexpr (DPL == 2) *(uint16_t *)(kdst + s2 * D + lane * 2) = (uint16_t)c;
-                else kdst[s2 * D + lane] = (uint8_t)c;
-            }
-        } else if (mine) {
-            // 8 codes per 16-byte bf16 word
-#pragma unroll
-            for (int w = 0; w < QW; ++w) {
-                uint32_t c[2] = {0u, 0u};
-#pragma unroll
-                for (int x = 0; x < 4; ++x) {
-                    const uint32_t lo8 = f32_to_e4m3(quotient(bf16_bits_to_f32(kw[w][x] & 0xFFFFu), dk));
-                    const uint32_t hi8 = f32_to_e4m3(quotient(bf16_bits_to_f32(kw[w][x] >> 16), dk));
-                    c[x >> 1] |= (lo8 | (hi8 << 8)) << (16 * (x & 1));
-                }
-                *(u32x2_t *)(kdst + m * D + part * (D / 4) + 8 * w) = (u32x2_t){c[0], c[1]};
+        for (int w = 0; w < SL; ++w) {
+            vc[w] = (u32x2_t){0u, 0u};
+            if (mine[w]) {   // one slot of a decode row: the other SL - 1 are skipped
+                *(u32x2_t *)(kdst + w * D) = e4m3x8(kw[w], dk);
+                vc[w] = e4m3x8(vw[w], dv);
             }
         }
-        auto vcode = [&](int s2, int e) -> uint32_t {
-            return f32_to_e4m3(quotient(bf16_bits_to_f32((col[s2] >> (16 * e)) & 0xFFFFu), dv));
-        };
 #pragma unroll
-        for (int e = 0; e < DPL; ++e) {
-            uint8_t *row = vdst + (lane * DPL + e) * 16;
-            if (full) {
-                uint32_t pk[4];
-#pragma unroll
-                for (int m2 = 0; m2 < 4; ++m2)
-                    pk[m2] = vcode(4 * m2, e) | (vcode(4 * m2 + 1, e) << 8) |
-                             (vcode(4 * m2 + 2, e) << 16) | (vcode(4 * m2 + 3, e) << 24);
-                *(u32x4_t *)row = (u32x4_t){pk[0], pk[1], pk[2], pk[3]};
+        for (int x = 0; x < 2; ++x) {
+            // 4 values x SL slots of bytes, transposed
+            const uint32_t p01 = bytes(vc[1][x], vc[0][x], 0x05010400u);   // d0: s0 s1, d1: s0 s1
+            const uint32_t q01 = bytes(vc[1][x], vc[0][x], 0x07030602u);   // d2, d3
+            if constexpr (SL == 4) {
+                const uint32_t p23 = bytes(vc[SL - 1][x], vc[SL - 2][x], 0x05010400u);
+                const uint32_t q23 = bytes(vc[SL - 1][x], vc[SL - 2][x], 0x07030602u);
+                *(uint32_t *)(vl + (4 * x + 0) * TL::ROW) = bytes(p23, p01, 0x05040100u);
+                *(uint32_t *)(vl + (4 * x + 1) * TL::ROW) = bytes(p23, p01, 0x07060302u);
+                *(uint32_t *)(vl + (4 * x + 2) * TL::ROW) = bytes(q23, q01, 0x05040100u);
+                *(uint32_t *)(vl + (4 * x + 3) * TL::ROW) = bytes(q23, q01, 0x07060302u);
             } else {
-                // the written slots only (the same for the whole wave): a decode
-                // row's unit quantises one slot, not sixteen
-#pragma unroll
-                for (int s2 = 0; s2 < 16; ++s2)
-                    if (s2 >= m_lo && s2 < m_hi) row[s2] = (uint8_t)vcode(s2, e);
+                *(uint16_t *)(vl + (4 * x + 0) * TL::ROW) = (uint16_t)p01;
+                *(uint16_t *)(vl + (4 * x + 1) * TL::ROW) = (uint16_t)(p01 >> 16);
+                *(uint16_t *)(vl + (4 * x + 2) * TL::ROW) = (uint16_t)q01;
+                *(uint16_t *)(vl + (4 * x + 3) * TL::ROW) = (uint16_t)(q01 >> 16);
             }
         }
     }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    // this lane's 16-byte units of the V tile hold slots u0 ..: all 16 of a
+    // row (e4m3) or half of them; those written now come from LDS
+    const int u0 = FP8 ? 0 : 8 * (lane & 1);
+    constexpr int PER = FP8 ? 4 : 2;   // slots per 32-bit word
+    u32x4_t keep;
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+        uint32_t m = 0;
+#pragma unroll
+        for (int y = 0; y < PER; ++y)
+            if ((uint32_t)(u0 + PER * x + y - m0) >= (uint32_t)n)
+                m |= (FP8 ? 0xFFu : 0xFFFFu) << (32 / PER * y);
+        keep[x] = m;
+    }
+#pragma unroll
+    for (int i = 0; i < NU; ++i) {
+        const int off = i * 1024 + 16 * lane;   // bytes into the tile
+        u32x4_t v = *(const u32x4_t *)(lds + off / (8 * TL::ROW) * TL::CHUNK + off % (8 * TL::ROW));
+        if (!full) v = (v & ~keep) | (old[i] & keep);
+        *(u32x4_t *)(vdst + i * 1024) = v;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
 }
 
+// Block j of row r, whose first new token is t0 at position p0 of L.
+template <int D, bool FP8>
+__device__ __forceinline__ void append_unit(const AppendArgs &a, int r, int j, int h, int t0, int p0,
+                                            int L, int lane, uint8_t *lds) {
+    if (j >= a.max_blocks_per_row) return;
+    const int blk = a.block_tables[(int64_t)r * a.max_blocks_per_row + j];
+    if (blk < 0 || blk >= a.num_blocks) return;
+    const int lo = max(p0, 16 * j), n = min(L, 16 * j + 16) - lo;   // tokens written
+    append_block<D, FP8>(a, blk, h, (int64_t)t0 + (lo - p0), lo & 15, n, lane, lds);
+}
+
+// A row of q new tokens writes at most q / 16 + 2 blocks, so with its units
+// numbered from q_start / 16 + 2 row no two rows' numbers meet, and a wave
+// finds the row of its number from q_start alone: 64 rows probed per load.
+// No scan, no barrier: rows of any mix of lengths take T / 16 + 2 B waves per
+// head, and a wave waits for one load (two past 64 rows) more than in the
+// direct form below.  (With a scan of all rows in every workgroup the e4m3
+// batch above took 25.4 us; with a loop over units, whose hoisted addresses
+// cost a wave per SIMD, 18.3 us.)
 template <int D, bool FP8>
 __global__ __launch_bounds__(256) void append_kernel(AppendArgs a) {
-    __shared__ int32_t pre[kAppWin];                  // exclusive prefix of written blocks
-    __shared__ int32_t rt0[kAppWin], rp0[kAppWin], rL[kAppWin];   // first token, start, length
-    __shared__ int32_t wsum[4];
-    __shared__ __attribute__((aligned(16))) uint16_t vstage[4][16 * D];
+    __shared__ __attribute__((aligned(16))) uint8_t vstage[4][AppendTile<D, FP8>::BYTES];
     const int lane = threadIdx.x & 63;
-    const int64_t gw = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int64_t nw = (int64_t)gridDim.x * 4;
-    const int H = a.num_kv_heads;
-    int64_t done = 0;  // units of earlier windows
-    for (int r0 = 0; r0 < a.num_rows; r0 += kAppWin) {
-        const int nr = min(kAppWin, a.num_rows - r0);
-        for (int i = threadIdx.x; i < nr; i += 256) {
-            const int r = r0 + i;
-            const int q = a.q_start[r + 1] - a.q_start[r];
-            const int L = a.seq_lens[r];
-            const int p0 = L - q;
-            const int jlast = min((L - 1) / 16, a.max_blocks_per_row - 1);
-            pre[i] = (q > 0 && p0 >= 0 && jlast >= p0 / 16) ? jlast - p0 / 16 + 1 : 0;
-            rt0[i] = a.q_start[r];
-            rp0[i] = p0;
-            rL[i] = L;
-        }
-        __syncthreads();
-        const int nblk = block_scan_window(pre, nr, wsum);
-        const int64_t units = (int64_t)nblk * H;
-        // this wave's units of the window: global indices done + u = gw (mod nw)
-        int64_t u = (gw - done) % nw;
-        if (u < 0) u += nw;
-        for (; u < units; u += nw) {
-            const int bu = (int)(u / H);
-            const int h = (int)(u - (int64_t)bu * H);
-            int lo = 0, hi = nr - 1;  // last row i with pre[i] <= bu
-            while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if (pre[mid] <= bu) lo = mid;
-                else hi = mid - 1;
-            }
-            const int p0 = rp0[lo];
-            append_unit<D, FP8>(a, r0 + lo, p0 / 16 + (bu - pre[lo]), h, lane, vstage[threadIdx.x >> 6],
-                                rt0[lo], p0, rL[lo]);
-        }
-        done += units;
-        __syncthreads();  // pre is rewritten by the next window
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t unit = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * 4 + wave;
+    if (unit >= a.n_units) return;
+    const uint32_t H = a.num_kv_heads;
+    const int B = a.num_rows;
+    const int64_t u = unit >> 32 ? unit / H : (int64_t)((uint32_t)unit / H);
+    const int h = (int)(unit - u * H);
+    int r = 0;   // last row whose numbers start at or before u
+    for (int n = B;;) {
+        const int step = (n + 63) >> 6, i = r + lane * step;
+        const bool at = lane * step < n && (int64_t)(a.q_start[i < B ? i : 0] >> 4) + 2 * (int64_t)i <= u;
+        const int k = max(__popcll(__ballot(at)), 1) - 1;
+        r += k * step;
+        if (step == 1) break;
+        n = min(step, n - k * step);
     }
+    r = __builtin_amdgcn_readfirstlane(r);
+    const int t0 = a.q_start[r];
+    const int q = a.q_start[r + 1] - t0;
+    const int L = a.seq_lens[r];
+    const int p0 = L - q;
+    const int64_t k = u - ((t0 >> 4) + 2 * (int64_t)r);
+    if (q <= 0 || p0 < 0 || k < 0 || k > (L - 1) / 16 - p0 / 16) return;
+    append_unit<D, FP8>(a, r, p0 / 16 + (int)k, h, t0, p0, L, lane, vstage[wave]);
 }
 
-// Direct form for batches whose rows write few blocks each (decode-heavy):
-// one wave per (row, k-th written block, KV head) of a padded grid, no scan,
-// no LDS, so many waves stay resident.  Same results as append_kernel.
+// Direct form for batches whose rows write about as many blocks each (decode
+// rows above all): one wave per (row, k-th written block, KV head).
 template <int D, bool FP8>
 __global__ __launch_bounds__(256) void append_rows_kernel(AppendArgs a) {
+    __shared__ __attribute__((aligned(16))) uint8_t vstage[4][AppendTile<D, FP8>::BYTES];
     const int lane = threadIdx.x & 63;
-    const int64_t unit = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (unit >= a.n_units) return;
-    const int H = a.num_kv_heads;
-    const int h = (int)(unit % H);
-    const int64_t rest = unit / H;
-    const int k = (int)(rest % a.blocks_per_row);
-    const int r = (int)(rest / a.blocks_per_row);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t unit = blockIdx.x * 4u + wave;
+    if (unit >= (uint32_t)a.n_units) return;
+    const uint32_t H = a.num_kv_heads, bpr = a.blocks_per_row;
+    const uint32_t rest = unit / H;
+    const int h = (int)(unit - rest * H);
+    const int r = (int)(rest / bpr), k = (int)(rest - (rest / bpr) * bpr);
     const int t0 = a.q_start[r];
     const int q = a.q_start[r + 1] - t0;
     const int L = a.seq_lens[r];
     const int p0 = L - q;
     if (q <= 0 || p0 < 0) return;
     const int j = p0 / 16 + k;
-    if (j > (L - 1) / 16 || j >= a.max_blocks_per_row) return;
-    const int blk = a.block_tables[(int64_t)r * a.max_blocks_per_row + j];
-    if (blk < 0 || blk >= a.num_blocks) return;
-    const int lo = max(p0, 16 * j), n = min(L, 16 * j + 16) - lo;   // tokens written
-    const int64_t tok_stride = (int64_t)H * D;
-    const int64_t src = (int64_t)(t0 + lo - p0) * tok_stride + (int64_t)h * D;
-    const int64_t tile = ((int64_t)blk * H + h) * 16 * D;
-    constexpr int LPT = D / 8, TPP = 64 / LPT;   // K: lanes of 16 bytes per row, rows per pass
-    constexpr int DPL = D / 64;                  // V: d values per lane
-    const int kr = lane / LPT, kc = (lane % LPT) * 8;
-    if constexpr (!FP8) {
-        uint16_t *kdst = (uint16_t *)a.k + tile;
-        uint16_t *vdst = (uint16_t *)a.v + tile;
-        for (int i = kr; i < n; i += TPP)
-            *(u32x4_t *)(kdst + ((lo + i) & 15) * D + kc) =
-                *(const u32x4_t *)(a.k_new + src + i * tok_stride + kc);
-        for (int i = 0; i < n; ++i) {
-            const uint16_t *vp = a.v_new + src + i * tok_stride + lane * DPL;
-            const uint32_t w = DPL == 2 ? *(const uint32_t *)vp : (uint32_t)*vp;
-            const int slot = (lo + i) & 15;
-#pragma unroll
-            for (int e = 0; e < DPL; ++e) vdst[(lane * DPL + e) * 16 + slot] = (uint16_t)(w >> (16 * e));
-        }
-    } else {
-        uint8_t *kdst = (uint8_t *)a.k + tile;
-        uint8_t *vdst = (uint8_t *)a.v + tile;
-        const int64_t si = (int64_t)blk * H + h;
-        float sk, sv;
-        if (16 * j >= p0) {  // slot 0 written by this call: fresh scales
-            float ak = 0.f, av = 0.f;
-            for (int i = 0; i < n; ++i)
-#pragma unroll
-                for (int e = 0; e < DPL; ++e) {
-                    const int d = lane * DPL + e;
-                    ak = fmaxf(ak, fabsf(bf16_bits_to_f32(a.k_new[src + i * tok_stride + d])));
-                    av = fmaxf(av, fabsf(bf16_bits_to_f32(a.v_new[src + i * tok_stride + d])));
-                }
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) {
-                ak = fmaxf(ak, __shfl_xor(ak, off));
-                av = fmaxf(av, __shfl_xor(av, off));
-            }
-            sk = ak == 0.f ? 1.f : ak / 448.0f;
-            sv = av == 0.f ? 1.f : av / 448.0f;
-            if (lane == 0) {
-                a.k_scale[si] = sk;
-                a.v_scale[si] = sv;
-            }
-        } else {
-            sk = a.k_scale[si];
-            sv = a.v_scale[si];
-        }
-        const Recip dk = recip_of(sk), dv = recip_of(sv);
-        for (int i = 0; i < n; ++i) {
-            const int slot = (lo + i) & 15;
-#pragma unroll
-            for (int e = 0; e < DPL; ++e) {
-                const int d = lane * DPL + e;
-                kdst[slot * D + d] =
-                    (uint8_t)f32_to_e4m3(quotient(bf16_bits_to_f32(a.k_new[src + i * tok_stride + d]), dk));
-                vdst[d * 16 + slot] =
-                    (uint8_t)f32_to_e4m3(quotient(bf16_bits_to_f32(a.v_new[src + i * tok_stride + d]), dv));
-            }
-        }
-    }
+    if (j > (L - 1) / 16) return;
+    append_unit<D, FP8>(a, r, j, h, t0, p0, L, lane, vstage[wave]);
 }
 
 // --------------------------------------------------------------- block copy
@@ -1725,11 +1646,9 @@ hipError_t launch_append(const AppendArgs &a, int head_dim, bool fp8, hipStream_
         else hipLaunchKernelGGL((append_rows_kernel<128, true>), grid, block, 0, s, d);
         return hipGetLastError();
     }
-    // one unit per wave where possible; every workgroup scans all rows, so
-    // the grid shrinks as rows grow (waves then loop over units)
-    const int64_t scan_cap = std::max<int64_t>(1024, (int64_t(1) << 22) / (a.num_rows + 1));
-    const int64_t wg = std::min<int64_t>((a.n_units + 3) / 4, scan_cap);
-    const dim3 grid((unsigned)wg);
+    // (a launch holds fewer than 2^32 threads in x)
+    const int64_t wg = (a.n_units + 3) / 4, gx = std::min<int64_t>(wg, 1 << 22);
+    const dim3 grid((unsigned)gx, (unsigned)((wg + gx - 1) / gx));
     if (head_dim == 64 && !fp8) hipLaunchKernelGGL((append_kernel<64, false>), grid, block, 0, s, a);
     else if (head_dim == 64) hipLaunchKernelGGL((append_kernel<64, true>), grid, block, 0, s, a);
     else if (!fp8) hipLaunchKernelGGL((append_kernel<128, false>), grid, block, 0, s, a);
