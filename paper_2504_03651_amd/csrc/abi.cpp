@@ -197,19 +197,31 @@ PlanOptions plan_options(const echo_kv_pool_t *pool) {
     return o;
 }
 
-int plan_for(const echo_kv_pool_t *pool, const echo_batch_t *batch, int32_t num_q_heads,
-             Plan &plan) {
+// Checks shared by both planning modes.
+int check_attn_args(const echo_kv_pool_t *pool, const echo_batch_t *batch, int32_t num_q_heads) {
     int rc = check_pool(pool);
     if (rc) return rc;
     rc = check_batch(pool, batch, false);
     if (rc) return rc;
-    if (batch->num_rows > 0 && !has_mirrors(batch))
-        return fail(ECHO_E_INVALID, "echo_attn_mixed needs the host mirrors of the batch");
     if (num_q_heads <= 0 || num_q_heads % pool->num_kv_heads != 0)
         return fail(ECHO_E_INVALID, "num_q_heads %d is not a multiple of num_kv_heads %d",
                     num_q_heads, pool->num_kv_heads);
     if (num_q_heads / pool->num_kv_heads > kPrefillQueries)
         return fail(ECHO_E_UNSUPPORTED, "more than %d query heads per KV head", kPrefillQueries);
+    return ECHO_OK;
+}
+
+// The host plan of a checked batch that has rows and mirrors.
+int plan_checked(const echo_kv_pool_t *pool, const echo_batch_t *batch, int32_t num_q_heads,
+                 Plan &plan) {
+    return build_plan(host_batch(batch), pool->num_kv_heads, num_q_heads, pool->head_dim,
+                      plan_options(pool), plan);
+}
+
+int plan_for(const echo_kv_pool_t *pool, const echo_batch_t *batch, int32_t num_q_heads,
+             Plan &plan) {
+    const int rc = check_attn_args(pool, batch, num_q_heads);
+    if (rc) return rc;
     if (batch->num_rows == 0) {
         plan.desc.clear();
         plan.merge_ptr.assign(1, 0);
@@ -218,8 +230,9 @@ int plan_for(const echo_kv_pool_t *pool, const echo_batch_t *batch, int32_t num_
         plan.layout.total_words = 64;
         return ECHO_OK;
     }
-    return build_plan(host_batch(batch), pool->num_kv_heads, num_q_heads, pool->head_dim,
-                      plan_options(pool), plan);
+    if (!has_mirrors(batch))
+        return fail(ECHO_E_INVALID, "echo_attn_mixed needs the host mirrors of the batch");
+    return plan_checked(pool, batch, num_q_heads, plan);
 }
 
 // Shortest XCD run (log2 of decode workgroups) for a plan: the waves that
@@ -451,20 +464,6 @@ int launch_attention(const echo_kv_pool_t *pool, const echo_batch_t *batch, cons
     return ECHO_OK;
 }
 
-// Checks shared by both planning modes.
-int check_attn_args(const echo_kv_pool_t *pool, const echo_batch_t *batch, int32_t num_q_heads) {
-    int rc = check_pool(pool);
-    if (rc) return rc;
-    rc = check_batch(pool, batch, false);
-    if (rc) return rc;
-    if (num_q_heads <= 0 || num_q_heads % pool->num_kv_heads != 0)
-        return fail(ECHO_E_INVALID, "num_q_heads %d is not a multiple of num_kv_heads %d",
-                    num_q_heads, pool->num_kv_heads);
-    if (num_q_heads / pool->num_kv_heads > kPrefillQueries)
-        return fail(ECHO_E_UNSUPPORTED, "more than %d query heads per KV head", kPrefillQueries);
-    return ECHO_OK;
-}
-
 // The device-built plan (no host mirrors): two planning kernels, then the
 // attention kernels reading their counts from the plan's header.
 int attn_device_planned(const echo_kv_pool_t *pool, const echo_batch_t *batch, const void *q,
@@ -533,6 +532,61 @@ int attn_device_planned(const echo_kv_pool_t *pool, const echo_batch_t *batch, c
     a.waves_per_desc = L.waves_per_desc;
     a.run_log2 = 0;
     a.pf_max_blocks = L.pf_max_blocks;
+    return launch_attention(pool, batch, q, num_q_heads, sm_scale, out, a, s, ev);
+}
+
+// Enqueues a host-planned call of checked arguments.
+int attn_planned(const echo_kv_pool_t *pool, const echo_batch_t *batch, const void *q,
+                 int32_t num_q_heads, float sm_scale, float *out, void *workspace,
+                 size_t workspace_bytes, void *host_workspace, size_t host_workspace_bytes,
+                 hipStream_t s, const Plan &plan) {
+    const PlanLayout &L = plan.layout;
+    int32_t pf_blocks = 0;
+    for (const PrefillDesc &d : plan.pdesc)
+        pf_blocks = std::max(pf_blocks, (d.key_end + kBlock - 1) / kBlock - d.key_begin / kBlock);
+    if (pf_blocks > prefill_max_blocks(pool->head_dim))
+        return fail(ECHO_E_UNSUPPORTED, "prefill row of %d blocks exceeds the %d-block limit",
+                    pf_blocks, prefill_max_blocks(pool->head_dim));
+    const size_t need = (size_t)L.total_words * 4;
+    if (!workspace || workspace_bytes < need)
+        return fail(ECHO_E_WORKSPACE, "workspace of %zu bytes, need %zu", workspace_bytes, need);
+    if (((uintptr_t)workspace & 255u) != 0)
+        return fail(ECHO_E_WORKSPACE, "workspace must be 256-byte aligned");
+    void *staged = nullptr;
+    int rc = check_host_workspace(host_workspace, host_workspace_bytes, (size_t)L.upload_words * 4,
+                              &staged);
+    if (rc) return rc;
+    hipEvent_t *ev = nullptr;
+    rc = profile_events(&ev);
+    if (rc) return rc;
+    g_prof.valid = false;
+    // every check is done: pack the plan into the host workspace and enqueue
+    pack_plan(plan, host_workspace);
+    hipError_t e;
+    if (ev && (e = hipEventRecord(ev[0], s)) != hipSuccess) return hip_fail(e, "hipEventRecord");
+    if ((e = launch_plan_upload(staged, workspace, L.upload_words, s)) != hipSuccess)
+        return hip_fail(e, "plan upload launch");
+    if (ev && (e = hipEventRecord(ev[1], s)) != hipSuccess) return hip_fail(e, "hipEventRecord");
+
+    int32_t *w = (int32_t *)workspace;
+    AttnLaunch a;
+    a.desc = (const WorkDesc *)(w + L.off_desc);
+    a.pdesc = (const PrefillDesc *)(w + L.off_pdesc);
+    a.tok_list = w + L.off_tok_list;
+    a.klim = w + L.off_klim;
+    a.merge_tok = w + L.off_merge_tok;
+    a.merge_ptr = w + L.off_merge_ptr;
+    a.merge_ent = w + L.off_merge_ent;
+    a.part_lse = (float *)(w + L.off_part_lse);
+    a.part_o = (float *)(w + L.off_part_o);
+    a.n_desc = L.n_desc;
+    a.n_merge_rows = L.n_merge_rows;
+    a.n_pdesc_grid = plan.pdesc_grid;
+    a.head_chunks = plan.head_chunks;
+    a.heads_per_chunk = plan.heads_per_chunk;
+    a.waves_per_desc = plan.waves_per_desc;
+    a.run_log2 = run_log2_for(plan.sibling_waves);
+    a.pf_max_blocks = pf_blocks;
     return launch_attention(pool, batch, q, num_q_heads, sm_scale, out, a, s, ev);
 }
 
@@ -636,25 +690,44 @@ int echo_block_copy(const echo_kv_pool_t *pool, const int32_t *pairs, int32_t n_
     if (n_pairs == 0) return ECHO_OK;
     if (!pairs) return fail(ECHO_E_INVALID, "pairs is NULL");
     if (h_pairs) {
-        std::vector<int32_t> srcs, dsts;
-        srcs.reserve(n_pairs);
-        dsts.reserve(n_pairs);
+        // one pass with a stamp per block; only a batch that fails one of the
+        // later checks is sorted, to name the block it fails for
+        thread_local std::vector<uint32_t> stamp;
+        thread_local uint32_t epoch = 0;
+        if (stamp.size() < (size_t)pool->num_blocks) {
+            stamp.assign((size_t)pool->num_blocks, 0);
+            epoch = 0;
+        }
+        if (epoch > UINT32_MAX - 2) {
+            std::fill(stamp.begin(), stamp.end(), 0u);
+            epoch = 0;
+        }
+        const uint32_t is_src = ++epoch, is_dst = ++epoch;
+        bool twice = false, both = false;
         for (int32_t i = 0; i < n_pairs; ++i) {
             const int32_t s = h_pairs[2 * i], d = h_pairs[2 * i + 1];
             if (s < 0 || s >= pool->num_blocks || d < 0 || d >= pool->num_blocks)
                 return fail(ECHO_E_RANGE, "pair %d: (%d, %d) outside [0, %d)", i, s, d,
                             pool->num_blocks);
             if (s == d) return fail(ECHO_E_INVALID, "pair %d copies block %d onto itself", i, s);
-            srcs.push_back(s);
-            dsts.push_back(d);
+            both |= stamp[s] == is_dst || stamp[d] == is_src;
+            twice |= stamp[d] == is_dst;
+            if (stamp[s] != is_dst) stamp[s] = is_src;
+            stamp[d] = is_dst;
         }
-        std::sort(srcs.begin(), srcs.end());
-        std::sort(dsts.begin(), dsts.end());
-        if (std::adjacent_find(dsts.begin(), dsts.end()) != dsts.end())
-            return fail(ECHO_E_INVALID, "a destination block appears twice");
-        for (int32_t d : dsts)
-            if (std::binary_search(srcs.begin(), srcs.end(), d))
-                return fail(ECHO_E_INVALID, "block %d is both a source and a destination", d);
+        if (twice) return fail(ECHO_E_INVALID, "a destination block appears twice");
+        if (both) {
+            std::vector<int32_t> srcs, dsts;
+            for (int32_t i = 0; i < n_pairs; ++i) {
+                srcs.push_back(h_pairs[2 * i]);
+                dsts.push_back(h_pairs[2 * i + 1]);
+            }
+            std::sort(srcs.begin(), srcs.end());
+            std::sort(dsts.begin(), dsts.end());
+            for (int32_t d : dsts)
+                if (std::binary_search(srcs.begin(), srcs.end(), d))
+                    return fail(ECHO_E_INVALID, "block %d is both a source and a destination", d);
+        }
     }
     BlockCopyArgs a;
     a.k = pool->k;
@@ -684,7 +757,7 @@ size_t echo_attn_workspace_bytes(const echo_kv_pool_t *pool, const echo_batch_t 
         return (size_t)L.total_words * 4;
     }
     thread_local Plan plan;
-    if (plan_for(pool, batch, num_q_heads, plan) != ECHO_OK) return 0;
+    if (plan_checked(pool, batch, num_q_heads, plan) != ECHO_OK) return 0;
     return (size_t)plan.layout.total_words * 4;
 }
 
@@ -694,7 +767,7 @@ size_t echo_attn_host_workspace_bytes(const echo_kv_pool_t *pool, const echo_bat
     if (check_attn_args(pool, batch, num_q_heads) != ECHO_OK) return 0;
     if (batch->num_rows == 0 || !has_mirrors(batch)) return 0;
     thread_local Plan plan;
-    if (plan_for(pool, batch, num_q_heads, plan) != ECHO_OK) return 0;
+    if (plan_checked(pool, batch, num_q_heads, plan) != ECHO_OK) return 0;
     return (size_t)plan.layout.upload_words * 4;
 }
 
@@ -785,56 +858,10 @@ int echo_attn_mixed(const echo_kv_pool_t *pool, const echo_batch_t *batch, const
                                    workspace_bytes, s);
 
     thread_local Plan plan;
-    rc = plan_for(pool, batch, num_q_heads, plan);
+    rc = plan_checked(pool, batch, num_q_heads, plan);
     if (rc) return rc;
-    const PlanLayout &L = plan.layout;
-    int32_t pf_blocks = 0;
-    for (const PrefillDesc &d : plan.pdesc)
-        pf_blocks = std::max(pf_blocks, (d.key_end + kBlock - 1) / kBlock - d.key_begin / kBlock);
-    if (pf_blocks > prefill_max_blocks(pool->head_dim))
-        return fail(ECHO_E_UNSUPPORTED, "prefill row of %d blocks exceeds the %d-block limit",
-                    pf_blocks, prefill_max_blocks(pool->head_dim));
-    const size_t need = (size_t)L.total_words * 4;
-    if (!workspace || workspace_bytes < need)
-        return fail(ECHO_E_WORKSPACE, "workspace of %zu bytes, need %zu", workspace_bytes, need);
-    if (((uintptr_t)workspace & 255u) != 0)
-        return fail(ECHO_E_WORKSPACE, "workspace must be 256-byte aligned");
-    void *staged = nullptr;
-    rc = check_host_workspace(host_workspace, host_workspace_bytes, (size_t)L.upload_words * 4,
-                              &staged);
-    if (rc) return rc;
-    hipEvent_t *ev = nullptr;
-    rc = profile_events(&ev);
-    if (rc) return rc;
-    g_prof.valid = false;
-    // every check is done: pack the plan into the host workspace and enqueue
-    pack_plan(plan, host_workspace);
-    hipError_t e;
-    if (ev && (e = hipEventRecord(ev[0], s)) != hipSuccess) return hip_fail(e, "hipEventRecord");
-    if ((e = launch_plan_upload(staged, workspace, L.upload_words, s)) != hipSuccess)
-        return hip_fail(e, "plan upload launch");
-    if (ev && (e = hipEventRecord(ev[1], s)) != hipSuccess) return hip_fail(e, "hipEventRecord");
-
-    int32_t *w = (int32_t *)workspace;
-    AttnLaunch a;
-    a.desc = (const WorkDesc *)(w + L.off_desc);
-    a.pdesc = (const PrefillDesc *)(w + L.off_pdesc);
-    a.tok_list = w + L.off_tok_list;
-    a.klim = w + L.off_klim;
-    a.merge_tok = w + L.off_merge_tok;
-    a.merge_ptr = w + L.off_merge_ptr;
-    a.merge_ent = w + L.off_merge_ent;
-    a.part_lse = (float *)(w + L.off_part_lse);
-    a.part_o = (float *)(w + L.off_part_o);
-    a.n_desc = L.n_desc;
-    a.n_merge_rows = L.n_merge_rows;
-    a.n_pdesc_grid = plan.pdesc_grid;
-    a.head_chunks = plan.head_chunks;
-    a.heads_per_chunk = plan.heads_per_chunk;
-    a.waves_per_desc = plan.waves_per_desc;
-    a.run_log2 = run_log2_for(plan.sibling_waves);
-    a.pf_max_blocks = pf_blocks;
-    return launch_attention(pool, batch, q, num_q_heads, sm_scale, out, a, s, ev);
+    return attn_planned(pool, batch, q, num_q_heads, sm_scale, out, workspace, workspace_bytes,
+                        host_workspace, host_workspace_bytes, s, plan);
 }
 
 int echo_attn_mixed_static(const echo_kv_pool_t *pool, const echo_batch_t *batch, const void *q,

@@ -205,14 +205,28 @@ class DeviceBatch:
         self.sl = torch.from_numpy(self.h_sl).to(device)
         self.qs = torch.from_numpy(self.h_qs).to(device)
         self.kind = torch.from_numpy(self.h_kind).to(device)
+        self._addr = {}   # name -> (mirror array, its address)
+
+    def _mirror(self, name: str) -> int:
+        # numpy takes 1-2 us to give an array's address; the array it was taken
+        # of is kept beside it, so a mirror that was replaced is looked up again
+        a = getattr(self, name)
+        seen = self._addr.get(name)
+        if seen is None or seen[0] is not a:
+            seen = self._addr[name] = (a, a.ctypes.data)
+        return seen[1]
+
+    def __getstate__(self):
+        return {**self.__dict__, "_addr": {}}   # a copy's mirrors lie elsewhere
 
     def c(self) -> CBatch:
-        m = self.mirrors
-        return CBatch(self.num_rows, self.mbr, self.num_tokens, self.max_q_len, self.max_seq_len,
-                      self.bt.data_ptr(), self.sl.data_ptr(), self.qs.data_ptr(),
-                      self.kind.data_ptr(),
-                      _np_ptr(self.h_bt) if m else None, _np_ptr(self.h_sl) if m else None,
-                      _np_ptr(self.h_qs) if m else None, _np_ptr(self.h_kind) if m else None)
+        b = CBatch(self.num_rows, self.mbr, self.num_tokens, self.max_q_len, self.max_seq_len,
+                   self.bt.data_ptr(), self.sl.data_ptr(), self.qs.data_ptr(),
+                   self.kind.data_ptr())
+        if self.mirrors:
+            b.h_block_tables, b.h_seq_lens = self._mirror("h_bt"), self._mirror("h_sl")
+            b.h_q_start, b.h_row_kind = self._mirror("h_qs"), self._mirror("h_kind")
+        return b
 
 
 # ---------------------------------------------------------------- entry points
@@ -252,7 +266,8 @@ class HostWorkspace:
 
     def __init__(self, slots: int = 4):
         self._bufs = [(None, 0)] * slots
-        self._events = [None] * slots
+        self._events = [None] * slots     # events a buffer's next user waits for
+        self._spare = [None] * slots      # events that have been waited for, to record again
         self._next = 0
 
     def acquire(self, nbytes: int):
@@ -262,7 +277,7 @@ class HostWorkspace:
         ev = self._events[i]
         if ev is not None:
             ev.synchronize()
-            self._events[i] = None
+            self._events[i], self._spare[i] = None, ev
         ptr, size = self._bufs[i]
         if size < nbytes:
             L = lib()
@@ -282,9 +297,11 @@ class HostWorkspace:
     def release(self, slot: int, stream) -> None:
         """Record that the work enqueued on ``stream`` so far reads ``slot``."""
         import torch
-        ev = torch.cuda.Event()
+        ev = self._spare[slot]
+        if ev is None or ev.device != stream.device:
+            ev = torch.cuda.Event()
         ev.record(stream)
-        self._events[slot] = ev
+        self._events[slot], self._spare[slot] = ev, None
 
     def close(self) -> None:
         for i, (ptr, _) in enumerate(self._bufs):
@@ -294,6 +311,7 @@ class HostWorkspace:
                 lib().hipHostFree(ctypes.c_void_p(ptr))
         self._bufs = [(None, 0)] * len(self._bufs)
         self._events = [None] * len(self._bufs)
+        self._spare = [None] * len(self._bufs)
 
     def __del__(self):
         try:
@@ -322,17 +340,32 @@ def attn_mixed(pool: KVPool, batch: DeviceBatch, q, num_q_heads: int, sm_scale: 
     import torch
     cp, cb = pool.c(), batch.c()
     s = torch.cuda.current_stream() if stream is None else stream
-    hptr, hsize, slot = None, 0, None
-    if batch.mirrors and batch.num_rows:
-        hw = host_workspace or default_host_workspace()
+
+    def call(hptr, hsize):
+        return lib().echo_attn_mixed(ctypes.byref(cp), ctypes.byref(cb), q.data_ptr(),
+                                     int(num_q_heads), float(sm_scale), out.data_ptr(),
+                                     workspace.data_ptr(),
+                                     workspace.numel() * workspace.element_size(), hptr, hsize,
+                                     ctypes.c_void_p(s.cuda_stream))
+
+    if not (batch.mirrors and batch.num_rows):
+        _check(call(None, 0), "echo_attn_mixed")
+        return
+    # The size of a plan is known once it is made, so the call gets the ring's
+    # next buffer as it is; only a plan that does not fit it (the call has then
+    # enqueued nothing) asks for the size, which plans once more.
+    hw = host_workspace or default_host_workspace()
+    hptr, hsize, slot = hw.acquire(1)
+    code = call(hptr, hsize)
+    if code == ECHO_E_WORKSPACE:
+        detail = last_error()
         need = host_workspace_bytes(pool, batch, num_q_heads)
+        if need <= hsize:
+            raise EchoError(code, "echo_attn_mixed", detail)
         hptr, hsize, slot = hw.acquire(need)
-    _check(lib().echo_attn_mixed(ctypes.byref(cp), ctypes.byref(cb), q.data_ptr(),
-                                 int(num_q_heads), float(sm_scale), out.data_ptr(),
-                                 workspace.data_ptr(), workspace.numel() * workspace.element_size(),
-                                 hptr, hsize, ctypes.c_void_p(s.cuda_stream)), "echo_attn_mixed")
-    if slot is not None:
-        hw.release(slot, s)
+        code = call(hptr, hsize)
+    _check(code, "echo_attn_mixed")
+    hw.release(slot, s)
 
 
 def attn_mixed_static(pool: KVPool, batch: DeviceBatch, q, num_q_heads: int, sm_scale: float,

@@ -1,0 +1,44 @@
+"""The addresses a DeviceBatch passes for its host mirrors follow the arrays:
+also after a mirror was replaced, and in a copy of the batch (CPU)."""
+import copy
+import ctypes
+
+import numpy as np
+
+from paper_2504_03651_amd import echo
+from paper_2504_03651_amd import workload as W
+
+
+def _addresses(b):
+    c = b.c()
+    return c.h_block_tables, c.h_seq_lens, c.h_q_start, c.h_row_kind
+
+
+def _want(b):
+    return tuple(a.ctypes.data for a in (b.h_bt, b.h_sl, b.h_qs, b.h_kind))
+
+
+def test_mirror_addresses_follow_the_arrays():
+    b = echo.DeviceBatch(W.config1().batch, "cpu")
+    assert _addresses(b) == _want(b) == _addresses(b)
+    b.h_sl = b.h_sl + 0
+    assert _addresses(b) == _want(b)
+    for twin in (copy.copy(b), copy.deepcopy(b)):
+        assert _addresses(twin) == _want(twin)
+    b.mirrors = False
+    assert _addresses(b) == (None,) * 4
+
+
+def test_block_copy_pairs_are_checked_in_any_order():
+    # one pass over the pairs finds what sorting found: a destination twice, a
+    # block on both sides in either order, and accepts a source used twice
+    pool = echo.CPool(0x1000, 0x1000, None, None, 64, 2, 64, 16, echo.KV_BF16)
+
+    def call(pairs):
+        h = np.ascontiguousarray(pairs, np.int32)
+        return echo.lib().echo_block_copy(ctypes.byref(pool), 0x1000, len(h), h.ctypes.data, None)
+
+    for bad in ([(1, 5), (2, 5)], [(1, 5), (5, 6)], [(5, 6), (1, 5)], [(3, 3)],
+                [(1, 5), (2, 6), (7, 1)], [(1, 5), (2, 6), (6, 8), (9, 5)]):
+        assert call(bad) == echo.ECHO_E_INVALID, bad
+    assert call([(1, 64)]) == echo.ECHO_E_RANGE and call([(-1, 3)]) == echo.ECHO_E_RANGE
