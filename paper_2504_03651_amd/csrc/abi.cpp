@@ -367,7 +367,7 @@ struct AttnLaunch {
     int64_t n_desc = 0, n_merge_rows = 0;
     int32_t n_pdesc_grid = 0;     // prefill descriptors that get workgroups (a capacity with counts)
     int32_t head_chunks = 1, heads_per_chunk = 1, waves_per_desc = 1, run_log2 = 0,
-            pf_max_blocks = 0;
+            pf_max_blocks = 0, num_cus = 256;
 };
 
 int launch_attention(const echo_kv_pool_t *pool, const echo_batch_t *batch, const void *q,
@@ -443,7 +443,7 @@ int launch_attention(const echo_kv_pool_t *pool, const echo_batch_t *batch, cons
     // pair still costs GPU time between the two records)
     if (pf.n_logical > 0) {
         if (ev && (e = hipEventRecord(ev[2], s)) != hipSuccess) return hip_fail(e, "hipEventRecord");
-        if ((e = launch_prefill(pf, D, fp8, s)) != hipSuccess) return hip_fail(e, "prefill launch");
+        if ((e = launch_prefill(pf, D, fp8, w.num_cus, s)) != hipSuccess) return hip_fail(e, "prefill launch");
         if (ev && (e = hipEventRecord(ev[3], s)) != hipSuccess) return hip_fail(e, "hipEventRecord");
     }
     if (a.n_waves > 0) {
@@ -532,6 +532,7 @@ int attn_device_planned(const echo_kv_pool_t *pool, const echo_batch_t *batch, c
     a.waves_per_desc = L.waves_per_desc;
     a.run_log2 = 0;
     a.pf_max_blocks = L.pf_max_blocks;
+    a.num_cus = plan_options(pool).num_cus;
     return launch_attention(pool, batch, q, num_q_heads, sm_scale, out, a, s, ev);
 }
 
@@ -587,6 +588,7 @@ int attn_planned(const echo_kv_pool_t *pool, const echo_batch_t *batch, const vo
     a.waves_per_desc = plan.waves_per_desc;
     a.run_log2 = run_log2_for(plan.sibling_waves);
     a.pf_max_blocks = pf_blocks;
+    a.num_cus = plan_options(pool).num_cus;
     return launch_attention(pool, batch, q, num_q_heads, sm_scale, out, a, s, ev);
 }
 

@@ -781,7 +781,8 @@ typedef __attribute__((address_space(3))) void lds_void_t;
 
 // One prefill descriptor di (a tile's tokens, or a piece of their keys) for
 // KV head kvh; all kPfThreads threads of the workgroup take part.
-template <int D, bool FP8>
+// DENSE (head_dim 64): two workgroups per CU, see prefill_kernel.
+template <int D, bool FP8, bool DENSE>
 __device__ __forceinline__ void prefill_piece(const PrefillArgs &a, int kvh, int di) {
     typedef KV<FP8> kv;
     typedef typename kv::T KT;
@@ -887,7 +888,8 @@ __device__ __forceinline__ void prefill_piece(const PrefillArgs &a, int kvh, int
     // tile, a step ahead, and made scalar) changes.
     static_assert((32 * D) % (NJ * 1024) == 0, "a wave's copies stay inside one block");
     const int bsel = wave * NJ * 1024 / (32 * D);
-    int k_off[NJ], v_off[NJ];
+    // (unsigned for DENSE: a scalar base and a 32-bit offset, fewer registers)
+    std::conditional_t<DENSE, uint32_t, int> k_off[NJ], v_off[NJ];
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
         const int off = (wave * NJ + j) * 1024 + 16 * lane;   // byte offset in the K / V region
@@ -1058,7 +1060,7 @@ __device__ __forceinline__ void prefill_piece(const PrefillArgs &a, int kvh, int
         for (int nn = 0; nn < 2; ++nn)
             lacc[nn] = mfma_pv(ones, pf[nn], lacc[nn]);
     };
-    auto tile = [&](int buf, int kt, bool masked) {
+    auto tile_piped = [&](int buf, int kt, bool masked) {
         const uint8_t *kl = lds + buf * LD::STAGE;
         const uint8_t *vl = kl + LD::KBYTES;
         f32x4_t s0[2][2], s1[2][2];
@@ -1097,6 +1099,41 @@ __device__ __forceinline__ void prefill_piece(const PrefillArgs &a, int kvh, int
                                  mc[1] > m_hi8[1] ? mc[1] : m_run[1]};
             rescale(mn);
         }
+    };
+
+    // The same tile a chunk at a time, for DENSE: half the live scores and
+    // probabilities, and the other workgroup's waves to co-issue with.
+    auto tile_serial = [&](int buf, int kt, bool masked) {
+        const uint8_t *kl = lds + buf * LD::STAGE;
+        const uint8_t *vl = kl + LD::KBYTES;
+        float mt[2] = {-INFINITY, -INFINITY};
+#pragma unroll
+        for (int ch = 0; ch < 2; ++ch) {
+            f32x4_t sc[2][2];
+            float m[2], f;
+            PT pr[2];
+            qk(kl, ch, sc);
+            prep(buf, kt, ch, masked, sc, m, f);
+            if (__any(m[0] > m_hig[0] || m[1] > m_hig[1])) {
+                const float mn[2] = {fmaxf(m_run[0], wave_max_xor16_32(m[0])),
+                                     fmaxf(m_run[1], wave_max_xor16_32(m[1]))};
+                rescale(mn);
+            }
+            expo(sc, pr, f);
+            pv(vl, ch, pr);
+            mt[0] = vmax(mt[0], m[0]);
+            mt[1] = vmax(mt[1], m[1]);
+        }
+        if (__any(mt[0] > m_hi8[0] || mt[1] > m_hi8[1])) {
+            const float mc[2] = {wave_max_xor16_32(mt[0]), wave_max_xor16_32(mt[1])};
+            const float mn[2] = {mc[0] > m_hi8[0] ? mc[0] : m_run[0],
+                                 mc[1] > m_hi8[1] ? mc[1] : m_run[1]};
+            rescale(mn);
+        }
+    };
+    auto tile = [&](int buf, int kt, bool masked) {
+        if constexpr (DENSE) tile_serial(buf, kt, masked);
+        else tile_piped(buf, kt, masked);
     };
 
     // Pipeline.  bf16: iteration kt loads the block ids of tile kt+3, starts
@@ -1146,10 +1183,21 @@ __device__ __forceinline__ void prefill_piece(const PrefillArgs &a, int kvh, int
     for (int kt = kt0; kt < nfull; ++kt) step(kt, false);
     for (int kt = max(nfull, kt0); kt < ntiles; ++kt) step(kt, true);
 
+    // DENSE takes the query columns again, from an index the compiler cannot
+    // see through: kept from the prologue they hold registers through the loop
+    int q0 = 32 * wave + c16;
+    if constexpr (DENSE) asm("" : "+v"(q0));
 #pragma unroll
     for (int nn = 0; nn < 2; ++nn) {
         const float l_tot = lacc[nn][0];
-        if (!qok[nn]) continue;
+        if constexpr (DENSE) {
+            const int qi = q0 + 16 * nn, tl = qi / G;
+            if (tl >= ntok) continue;
+            qtok[nn] = tok0 + tl;
+            qhead[nn] = kvh * G + (qi - tl * G);
+        } else if (!qok[nn]) {
+            continue;
+        }
         const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
         float *dst;
         if (part < 0) {
@@ -1157,7 +1205,7 @@ __device__ __forceinline__ void prefill_piece(const PrefillArgs &a, int kvh, int
         } else {
             // the slot the merge kernel reads for (token, head) of this piece:
             // part + (kvh * head_chunks + hc) * ntok * heads_per_chunk + token * nh + jh
-            const int qi = 32 * wave + 16 * nn + c16, tl = qi / G, hg = qi - tl * G;
+            const int qi = q0 + 16 * nn, tl = qi / G, hg = qi - tl * G;
             const int hc = hg / 16, jh = hg - 16 * hc;
             const int nh = min(a.heads_per_chunk, G - 16 * hc);
             const int64_t slot = part + (int64_t)(kvh * a.head_chunks + hc) * ntok * a.heads_per_chunk +
@@ -1173,7 +1221,7 @@ __device__ __forceinline__ void prefill_piece(const PrefillArgs &a, int kvh, int
 // One prefill workgroup: P is its physical workgroup index in the prefill
 // grid (8 * per_xcd workgroups).  Its descriptor may name a second one
 // (a piece of another tile's keys) that the workgroup runs next.
-template <int D, bool FP8>
+template <int D, bool FP8, bool DENSE>
 __device__ __forceinline__ void prefill_body(const PrefillArgs &a, int P) {
     const int L = (P % 8) * a.per_xcd + P / 8;  // consecutive logical tiles share an XCD
     if (L >= a.n_logical) return;
@@ -1181,7 +1229,7 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs &a, int P) {
     int di = L - kvh * a.n_pdesc;
     if (a.counts && di >= ro_load(a.counts, kHdrPdesc)) return;
     for (;;) {
-        prefill_piece<D, FP8>(a, kvh, di);
+        prefill_piece<D, FP8, DENSE>(a, kvh, di);
         const int next = __builtin_amdgcn_readfirstlane(((const int32_t *)(a.pdesc + di))[7]);
         if (next <= 0) break;
         __syncthreads();   // the next descriptor refills the LDS ring and block ids
@@ -1189,9 +1237,16 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs &a, int P) {
     }
 }
 
-template <int D, bool FP8>
-__global__ __launch_bounds__(kPfThreads, 8 / kPfWaves) void prefill_kernel(PrefillArgs a) {
-    prefill_body<D, FP8>(a, blockIdx.x);
+// One workgroup per CU at head_dim 128 (222-246 VGPRs).  At head_dim 64 half
+// the products meet the same softmax work, and the waves of one workgroup,
+// which a barrier per tile keeps in step, leave the matrix cores idle; DENSE
+// holds a wave to 128 VGPRs so that two workgroups share a CU, and overlaps one
+// workgroup's softmax with the other's products instead of pipelining the two
+// chunks of a tile.  12 prompts of 84-1,428 tokens (GQA 64/8), 0.52 -> 0.62
+// PFLOP/s: 168 -> 142 us, and 130 us with the longest tiles first.
+template <int D, bool FP8, bool DENSE>
+__global__ __launch_bounds__(kPfThreads, DENSE ? 4 : 1) void prefill_kernel(PrefillArgs a) {
+    prefill_body<D, FP8, DENSE>(a, blockIdx.x);
 }
 
 // -------------------------------------------------------------------- merge
@@ -1705,19 +1760,25 @@ static hipError_t raise_lds_limit(const void *f, std::atomic<uint64_t> &done) {
     return hipSuccess;
 }
 
-template <int D, bool FP8>
+template <int D, bool FP8, bool DENSE = false>
 static hipError_t launch_prefill_t(const PrefillArgs &p, hipStream_t s) {
     static std::atomic<uint64_t> attr_devices{0};
-    hipError_t e = raise_lds_limit((const void *)prefill_kernel<D, FP8>, attr_devices);
+    hipError_t e = raise_lds_limit((const void *)prefill_kernel<D, FP8, DENSE>, attr_devices);
     if (e != hipSuccess) return e;
     const int bytes = PfLds<D>::BYTES + 4 * p.max_blocks;
     const dim3 grid((unsigned)(8 * p.per_xcd)), block(kPfThreads);
-    hipLaunchKernelGGL((prefill_kernel<D, FP8>), grid, block, bytes, s, p);
+    hipLaunchKernelGGL((prefill_kernel<D, FP8, DENSE>), grid, block, bytes, s, p);
     return hipGetLastError();
 }
 
-hipError_t launch_prefill(const PrefillArgs &p, int head_dim, bool fp8, hipStream_t s) {
+hipError_t launch_prefill(const PrefillArgs &p, int head_dim, bool fp8, int num_cus, hipStream_t s) {
     if (p.n_logical <= 0) return hipSuccess;
+    // Two workgroups per CU pay past two rounds of CUs.  Measured (pipelined ->
+    // DENSE) at 272 and 312 workgroups 47.6 -> 53.3 and 54.7 -> 61.2 us, at 512
+    // 56.2 -> 57.2 and 95.0 -> 93.2, at 640 146.3 -> 125.7 and 38.7 -> 35.2, at
+    // 1,024 261 -> 221 and 54.0 -> 44.5.
+    if (head_dim == 64 && p.n_logical > 2 * (int64_t)num_cus)
+        return fp8 ? launch_prefill_t<64, true, true>(p, s) : launch_prefill_t<64, false, true>(p, s);
     if (head_dim == 64 && !fp8) return launch_prefill_t<64, false>(p, s);
     if (head_dim == 64) return launch_prefill_t<64, true>(p, s);
     if (!fp8) return launch_prefill_t<128, false>(p, s);

@@ -127,7 +127,7 @@ int prefill_max_blocks(int head_dim);
 // Attention launchers; each returns hipSuccess without launching when it
 // has no work.  The merge reads the partial results of both others, so it
 // runs after them.
-hipError_t launch_prefill(const PrefillArgs &p, int head_dim, bool fp8, hipStream_t s);
+hipError_t launch_prefill(const PrefillArgs &p, int head_dim, bool fp8, int num_cus, hipStream_t s);
 hipError_t launch_decode(const AttnArgs &a, int head_dim, bool fp8, hipStream_t s);
 hipError_t launch_merge(const MergeArgs &m, int head_dim, hipStream_t s);
 

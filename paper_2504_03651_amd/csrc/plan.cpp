@@ -16,6 +16,12 @@ struct Segment {
     int32_t key_end;   // one past the last key
 };
 
+// 4 log2 of a length, rounded down to its leading bits' quarter
+int32_t length_class(int32_t n) {
+    const int32_t e = 31 - __builtin_clz((uint32_t)n | 4u);
+    return 4 * e + (((uint32_t)n >> (e - 2)) & 3);
+}
+
 int64_t align_words(int64_t w, int64_t a) { return (w + a - 1) / a * a; }
 
 // Prefix trie over the read-only full blocks of decode rows.  Rows in
@@ -262,6 +268,18 @@ int build_plan(const HostBatch &b, int32_t Hkv, int32_t Hq, int32_t D, const Pla
             ++pf_tiles;
         }
     }
+    // More than two rounds at head_dim 64, where two workgroups share a CU: the
+    // longest key ranges first over all rows, so that the launch does not end
+    // on a long tile (12 prompts: 142 -> 130 us).  By quarters of a power of
+    // two, so that the tiles of rows of about one length stay together and
+    // share their keys in L2.  At head_dim 128, one workgroup per CU, the order
+    // by rows is the better one (12 prompts 139 us against 141; four rows of
+    // 32,768 keys sorted by exact length 4% slower).
+    if (D == 64 && pf_tiles * Hkv > 2 * (int64_t)opt.num_cus)
+        std::stable_sort(plan.pdesc.begin(), plan.pdesc.end(),
+                         [](const PrefillDesc &x, const PrefillDesc &y) {
+                             return length_class(x.key_end) > length_class(y.key_end);
+                         });
     // Workgroups for at most half the CUs leave the rest idle (a late chunk
     // of a long prompt is a handful of tiles over tens of thousands of keys):
     // cut key ranges longer than the average share of a CU into pieces at
