@@ -364,7 +364,7 @@ struct AttnLaunch {
     const int32_t *tok_list = nullptr, *klim = nullptr, *merge_tok = nullptr,
                   *merge_ptr = nullptr, *merge_ent = nullptr, *counts = nullptr;
     float *part_lse = nullptr, *part_o = nullptr;
-    int64_t n_desc = 0, n_merge_rows = 0;
+    int64_t n_desc = 0, n_merge_rows = 0, n_merge_wide = 0;
     int32_t n_pdesc_grid = 0;     // prefill descriptors that get workgroups (a capacity with counts)
     int32_t head_chunks = 1, heads_per_chunk = 1, waves_per_desc = 1, run_log2 = 0,
             pf_max_blocks = 0, num_cus = 256;
@@ -398,7 +398,9 @@ int launch_attention(const echo_kv_pool_t *pool, const echo_batch_t *batch, cons
     a.part_lse = w.part_lse;
     a.counts = w.counts;
     MergeArgs m;
-    m.n_waves = w.n_merge_rows * ((num_q_heads + 3) / 4);
+    m.n_rows = w.n_merge_rows;
+    m.n_wide = w.n_merge_wide;
+    m.n_waves = 0;
     m.counts = w.counts;
     m.num_q_heads = num_q_heads;
     m.head_chunks = w.head_chunks;
@@ -451,7 +453,7 @@ int launch_attention(const echo_kv_pool_t *pool, const echo_batch_t *batch, cons
         if ((e = launch_decode(a, D, fp8, s)) != hipSuccess) return hip_fail(e, "decode launch");
         if (ev && (e = hipEventRecord(ev[5], s)) != hipSuccess) return hip_fail(e, "hipEventRecord");
     }
-    if (m.n_waves > 0) {
+    if (m.n_rows > 0) {
         if (ev && (e = hipEventRecord(ev[6], s)) != hipSuccess) return hip_fail(e, "hipEventRecord");
         if ((e = launch_merge(m, D, s)) != hipSuccess) return hip_fail(e, "merge launch");
         if (ev && (e = hipEventRecord(ev[7], s)) != hipSuccess) return hip_fail(e, "hipEventRecord");
@@ -460,7 +462,7 @@ int launch_attention(const echo_kv_pool_t *pool, const echo_batch_t *batch, cons
     g_prof.launched[0] = true;
     g_prof.launched[1] = pf.n_logical > 0;
     g_prof.launched[2] = a.n_waves > 0;
-    g_prof.launched[3] = m.n_waves > 0;
+    g_prof.launched[3] = m.n_rows > 0;
     return ECHO_OK;
 }
 
@@ -582,6 +584,7 @@ int attn_planned(const echo_kv_pool_t *pool, const echo_batch_t *batch, const vo
     a.part_o = (float *)(w + L.off_part_o);
     a.n_desc = L.n_desc;
     a.n_merge_rows = L.n_merge_rows;
+    a.n_merge_wide = plan.merge_wide;
     a.n_pdesc_grid = plan.pdesc_grid;
     a.head_chunks = plan.head_chunks;
     a.heads_per_chunk = plan.heads_per_chunk;

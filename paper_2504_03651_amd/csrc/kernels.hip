@@ -1251,24 +1251,29 @@ __global__ __launch_bounds__(kPfThreads, DENSE ? 4 : 1) void prefill_kernel(Pref
 
 // -------------------------------------------------------------------- merge
 //
-// One wave per (merged token, 4 query heads): 16 lanes per head, each lane
-// owning D/16 consecutive elements of the head's output row.  A 16-lane group
-// takes its entries 16 at a time (one per lane: slot and lse loaded in
-// parallel), rescales its running sums to the new maximum, then adds the
-// entries' partial rows, four independent loads at a time.
+// Lanes in four 16-lane groups, each lane owning D/16 consecutive elements of a
+// head's output row.  A group takes its entries 16 at a time (one per lane:
+// slot and lse loaded in parallel), rescales its running sums to the new
+// maximum, then adds the entries' partial rows, four independent loads at a
+// time.  Bound by that chain of loads (entries -> lse -> rows, four deep for 16
+// entries) until the partial rows fill the memory's time, so a wave takes
+//   WIDE   one head of a token, every group a quarter of its entries, combined
+//          at the end: the shortest chain, for rows of many entries and for
+//          merges that leave the chip idle
+//   else   four heads of a token, a head per group: the fewest waves
+// (Eight loads at a time instead of four: 0.5-1 us slower, two waves per SIMD
+// fewer.)  8 decode rows of up to 64 entries: 7.0 -> 4.7 us; one row of 64
+// entries: 12.6 -> 6.7 us; 32 rows of up to 34 beside 320 tokens of two: 11.5 ->
+// 6.7 us.
 
-template <int D>
-__global__ __launch_bounds__(256) void merge_kernel(MergeArgs a) {
+template <int D, bool WIDE>
+__device__ __forceinline__ void merge_heads(const MergeArgs &a, int row, int h, int lane) {
     constexpr int PER = D / 16;   // floats per lane
     constexpr int NV = PER / 4;   // 16-byte loads per lane and partial row
-    const int lane = threadIdx.x & 63;
+    constexpr int BATCH = 4;
+    constexpr int GROUPS = WIDE ? 4 : 1;   // groups that share the entries
     const int c16 = lane & 15, base = lane & 48;
-    const int64_t m = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (m >= a.n_waves) return;
-    const int hgroups = (a.num_q_heads + 3) / 4;
-    const int row = (int)(m / hgroups);
-    if (a.counts && row >= ro_load(a.counts, kHdrMergeRows)) return;
-    const int h = 4 * (int)(m - (int64_t)row * hgroups) + (lane >> 4);
+    const int g = WIDE ? lane >> 4 : 0;
     const bool hok = h < a.num_q_heads;
     const int tok = a.merge_tok[row];
     const int e0 = a.merge_ptr[row], e1 = a.merge_ptr[row + 1];
@@ -1282,9 +1287,10 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeArgs a) {
 #pragma unroll
     for (int k = 0; k < NV; ++k) acc[k] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
     float mx = -INFINITY, wsum = 0.f;
-    for (int eb = e0; eb < e1; eb += 16) {
-        const int e = eb + c16;
-        int slot = 0;   // entries past the end (and heads past Hq) read slot 0 with weight 0
+    // every lane stays in the loop: the lane exchanges read all of them
+    for (int eb = e0; eb < e1; eb += 16 * GROUPS) {
+        const int e = eb + GROUPS * c16 + g;
+        int slot = 0;
         float lse = -INFINITY;
         if (hok && e < e1) {
             const int part = a.merge_ent[2 * e], sh = a.merge_ent[2 * e + 1];
@@ -1305,38 +1311,80 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeArgs a) {
 #pragma unroll
         for (int k = 0; k < NV; ++k) acc[k] *= alpha;
         mx = m_new;
-        const int n = min(16, e1 - eb);
+        const int most = min(16, (e1 - eb + GROUPS - 1) / GROUPS);   // entries of group 0
+        const int n = WIDE ? min(16, (e1 - eb - g + 3) >> 2) : most; // of this group
         auto load = [&](int i, f32x4_t (&v)[NV], float &wi) {
             const int si = __shfl(slot, base + i);
             wi = __shfl(w, base + i);
             const f32x4_t *po = (const f32x4_t *)(a.part_o + (int64_t)si * D + c16 * PER);
 #pragma unroll
-            for (int k = 0; k < NV; ++k) v[k] = po[k];
+            for (int k = 0; k < NV; ++k) {
+                if constexpr (WIDE) {
+                    v[k] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+                    if (i < n) v[k] = po[k];
+                } else {
+                    v[k] = po[k];
+                }
+            }
         };
         int i = 0;
-        for (; i + 4 <= n; i += 4) {
-            f32x4_t v[4][NV];
-            float wi[4];
+        for (; WIDE ? i < most : i + BATCH <= most; i += BATCH) {
+            f32x4_t v[BATCH][NV];
+            float wi[BATCH];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) load(i + j, v[j], wi[j]);
+            for (int j = 0; j < BATCH; ++j) load((i + j) & 15, v[j], wi[j]);
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
+            for (int j = 0; j < BATCH; ++j)
 #pragma unroll
-                for (int k = 0; k < NV; ++k) acc[k] += wi[j] * v[j][k];
+                for (int k = 0; k < NV; ++k) acc[k] += (!WIDE || i + j < n ? wi[j] : 0.f) * v[j][k];
         }
-        for (; i < n; ++i) {
-            f32x4_t v[NV];
-            float wi;
-            load(i, v, wi);
+        if constexpr (!WIDE)
+            for (; i < most; ++i) {
+                f32x4_t v[NV];
+                float wi;
+                load(i, v, wi);
 #pragma unroll
-            for (int k = 0; k < NV; ++k) acc[k] += wi * v[k];
+                for (int k = 0; k < NV; ++k) acc[k] += wi * v[k];
+            }
+    }
+    if constexpr (WIDE) {
+#pragma unroll
+        for (int off = 16; off <= 32; off <<= 1) {
+            const float om = __shfl_xor(mx, off);
+            const float m_new = fmaxf(mx, om);
+            const float m_use = m_new == -INFINITY ? 0.f : m_new;
+            const float alpha = exp2f(mx - m_use), beta = exp2f(om - m_use);
+            wsum = wsum * alpha + __shfl_xor(wsum, off) * beta;
+#pragma unroll
+            for (int k = 0; k < NV; ++k)
+#pragma unroll
+                for (int x = 0; x < 4; ++x)
+                    acc[k][x] = acc[k][x] * alpha + __shfl_xor(acc[k][x], off) * beta;
+            mx = m_new;
         }
+        if (g) return;
     }
     if (!hok) return;
     const float inv = wsum > 0.f ? 1.f / wsum : 0.f;
     f32x4_t *o = (f32x4_t *)(a.out + ((int64_t)tok * a.num_q_heads + h) * D + c16 * PER);
 #pragma unroll
     for (int k = 0; k < NV; ++k) o[k] = acc[k] * inv;
+}
+
+// The first a.n_wide rows go a head per wave, the others four.
+template <int D>
+__global__ __launch_bounds__(256) void merge_kernel(MergeArgs a) {
+    const int lane = threadIdx.x & 63;
+    const int64_t m = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (m >= a.n_waves) return;
+    const int64_t wide = a.n_wide * a.num_q_heads;
+    const int per = m < wide ? a.num_q_heads : (a.num_q_heads + 3) / 4;
+    const int64_t x = m < wide ? m : m - wide;
+    const int64_t r = x >> 32 ? x / per : (int64_t)((uint32_t)x / (uint32_t)per);
+    const int k = (int)(x - r * per), row = (int)(m < wide ? r : r + a.n_wide);
+    if (a.counts && row >= ro_load(a.counts, kHdrMergeRows)) return;
+    if (m < wide) merge_heads<D, true>(a, row, k, lane);
+    else merge_heads<D, false>(a, row, 4 * k + (lane >> 4), lane);
 }
 
 // ------------------------------------------------------- device-built plan
@@ -1785,6 +1833,11 @@ hipError_t launch_prefill(const PrefillArgs &p, int head_dim, bool fp8, int num_
     return launch_prefill_t<128, true>(p, s);
 }
 
+// Merges of at most this many (token, head) pairs give each a wave whatever its
+// entries: fewer waves than SIMDs x 2 (8,192 pairs of about four entries took
+// 11.8 us that way against 9.7, 2,048 pairs of six the same either way).
+constexpr int64_t kMergeWideWaves = 2048;
+
 // Decode launch shape: runs of 16 workgroups, or shorter so that there are
 // at least 64 runs, but never shorter than the run length the caller asks
 // for in b.run_log2 (at most 32 workgroups); the grid is a multiple of 8 runs
@@ -1812,10 +1865,13 @@ hipError_t launch_decode(const AttnArgs &a, int head_dim, bool fp8, hipStream_t 
 }
 
 hipError_t launch_merge(const MergeArgs &m, int head_dim, hipStream_t s) {
-    if (m.n_waves <= 0) return hipSuccess;
-    const dim3 grid((unsigned)((m.n_waves + 3) / 4)), block(256);
-    if (head_dim == 64) hipLaunchKernelGGL((merge_kernel<64>), grid, block, 0, s, m);
-    else hipLaunchKernelGGL((merge_kernel<128>), grid, block, 0, s, m);
+    if (m.n_rows <= 0) return hipSuccess;
+    MergeArgs b = m;
+    if (m.n_rows * m.num_q_heads <= kMergeWideWaves) b.n_wide = m.n_rows;
+    b.n_waves = b.n_wide * m.num_q_heads + (m.n_rows - b.n_wide) * ((m.num_q_heads + 3) / 4);
+    const dim3 grid((unsigned)((b.n_waves + 3) / 4)), block(256);
+    if (head_dim == 64) hipLaunchKernelGGL((merge_kernel<64>), grid, block, 0, s, b);
+    else hipLaunchKernelGGL((merge_kernel<128>), grid, block, 0, s, b);
     return hipGetLastError();
 }
 

@@ -68,7 +68,9 @@ struct PrefillArgs {
 };
 
 struct MergeArgs {
-    int64_t n_waves;                // merged rows * ceil(Hq / 4)
+    int64_t n_rows;                 // merged tokens (a capacity with counts)
+    int64_t n_wide;                 // leading rows that get a wave per head
+    int64_t n_waves;                // set by the launcher
     const int32_t *counts;          // device-built plan: its header (word 2 = merged rows)
     int32_t num_q_heads, head_chunks, heads_per_chunk, group;
     const int32_t *merge_tok, *merge_ptr;

@@ -184,12 +184,17 @@ int build_plan(const HostBatch &b, int32_t Hkv, int32_t Hq, int32_t D, const Pla
     // slice of nt tokens
     moff.assign((size_t)B, -1);
     int64_t n_ent = 0;
-    for (int32_t r : R) {
-        if (cnt[r] < 2) continue;
-        moff[r] = (int32_t)plan.merge_tok.size();
-        plan.merge_tok.push_back(b.q_start[r]);
-        plan.merge_ptr.push_back((int32_t)n_ent);
-        n_ent += cnt[r];
+    // the rows of many entries first: the merge gives each of their heads a wave
+    plan.merge_wide = 0;
+    for (const bool many : {true, false}) {
+        for (int32_t r : R) {
+            if (cnt[r] < 2 || (cnt[r] > kMergeManyEntries) != many) continue;
+            moff[r] = (int32_t)plan.merge_tok.size();
+            plan.merge_tok.push_back(b.q_start[r]);
+            plan.merge_ptr.push_back((int32_t)n_ent);
+            n_ent += cnt[r];
+        }
+        if (many) plan.merge_wide = (int32_t)plan.merge_tok.size();
     }
     plan.merge_ptr.push_back((int32_t)n_ent);
     plan.merge_ent.assign((size_t)(2 * n_ent), -1);

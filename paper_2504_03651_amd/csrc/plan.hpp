@@ -69,10 +69,7 @@ constexpr int kPrefillMinChainTiles = 2;  // fewest 64-key tiles moved to a chai
 // the bytes per block (a sweep of 16-128 blocks on the decode-only, mixed and
 // e4m3 batches).
 constexpr int64_t kSplitBytes = 384 * 1024;
-#ifndef ECHO_MIN_SPLIT
-#define ECHO_MIN_SPLIT 8
-#endif
-constexpr int kMinSplitBlocks = ECHO_MIN_SPLIT;        // shortest decode piece on small batches
+constexpr int kMinSplitBlocks = 8;        // shortest decode piece on small batches
 constexpr int kSplitTargetUnits = 2048;   // decode units below which pieces shrink
 #ifndef ECHO_EQ_GENS
 #define ECHO_EQ_GENS 3
@@ -95,6 +92,10 @@ constexpr int kDecodeWavesPerCu = 12;
 // one at 128, decode 0.442 -> 0.386 ms; batches that cannot get there keep
 // the default)
 constexpr int kOneGenerationStretch = ECHO_ONE_GEN_STRETCH;
+
+// Merge entries of a token from which its heads get a wave each: past 16 a
+// 16-lane group would walk them in several turns, a chain of loads each.
+constexpr int kMergeManyEntries = 16;
 
 // Wave w of the attention grid handles descriptor w / (Hkv * head_chunks),
 // KV head (w % (Hkv * head_chunks)) / head_chunks and head chunk
@@ -155,6 +156,7 @@ struct Plan {
     PlanLayout layout;
     PlanStats stats;
     int32_t waves_per_desc = 1;   // num_kv_heads * head_chunks
+    int32_t merge_wide = 0;       // leading merge rows of more than kMergeManyEntries entries
     int32_t sibling_waves = 0;    // most decode waves that read one shared key range
     int32_t head_chunks = 1;
     int32_t heads_per_chunk = 1;  // min(G, 16)
