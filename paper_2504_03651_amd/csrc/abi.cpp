@@ -176,6 +176,7 @@ PlanOptions plan_options(const echo_kv_pool_t *pool) {
     }();
     const int64_t block_bytes = 2 * (int64_t)kBlock * pool->head_dim *
                                 (pool->dtype == ECHO_KV_FP8_E4M3 ? 1 : 2);
+    o.light = block_bytes < 2 * (int64_t)kBlock * 128 * 2;
     o.split_blocks = split > 0 ? split : (int)std::max<int64_t>(1, kSplitBytes / block_bytes);
     // compute units of the current device (256 on MI355X; also the value
     // used by host-only calls made where no device is present)
@@ -500,6 +501,7 @@ int attn_device_planned(const echo_kv_pool_t *pool, const echo_batch_t *batch, c
     d.min_split_blocks = L.min_split;
     d.max_split_blocks = L.max_split;
     d.wave_slots = L.wave_slots;
+    d.light_steps = plan_options(pool).light;
     d.waves_per_desc = L.waves_per_desc;
     d.tile_tokens = L.tile_tokens;
     d.slots_per_desc = L.slots_per_desc;

@@ -1495,6 +1495,7 @@ __global__ __launch_bounds__(kPlanThreads) void dev_plan_kernel(DevPlanArgs a) {
     __shared__ int32_t row_len[kPlanThreads], row_t0[kPlanThreads], row_q[kPlanThreads];
     __shared__ PlanCount wsum[kPlanWaves];
     __shared__ int64_t wsum_l[kPlanWaves];
+    __shared__ int32_t pieces[kPlanWaves][64];
     __shared__ int bad_rows, used_pf;
     const int tid = threadIdx.x;
     const int B = a.num_rows;
@@ -1571,7 +1572,6 @@ __global__ __launch_bounds__(kPlanThreads) void dev_plan_kernel(DevPlanArgs a) {
         if ((tid & 63) == 0) wsum_l[tid >> 6] = mine;
         __syncthreads();
         for (int w = 0; w < kPlanWaves; ++w) blocks += wsum_l[w];
-        __syncthreads();   // wsum_l is rewritten
     }
     const int64_t units_cap = min<int64_t>(blocks * a.waves_per_desc / kSplitTargetUnits,
                                            a.max_split_blocks);
@@ -1581,27 +1581,37 @@ __global__ __launch_bounds__(kPlanThreads) void dev_plan_kernel(DevPlanArgs a) {
         lo = min(lo, max(a.min_split_blocks, (int)(((uint32_t)blocks + room - 1) / room)));
     int split = min(a.split_blocks, max(lo, (int)units_cap));
     if (B <= kPlanThreads) {
-        // each wave counts the pieces of one candidate length; two rounds of
-        // kPlanWaves candidates narrow the shortest one whose launch fits the chip
-        int hi = max(split, (int)units_cap);
-        for (int round = 0; round < 2; ++round) {
-            const int step = (hi - lo + kPlanWaves - 2) / (kPlanWaves - 1);
-            const int cand = min(lo + (tid >> 6) * step, hi);
-            int n = 0;
-            for (int r = tid & 63; r < B; r += 64) n += (row_np[r] + cand - 1) / cand;
+        // Waves of the launch for 64 piece lengths from lo to the longest, one
+        // per lane (the waves take the rows in turn); then, as the host planner
+        // does, the shortest length for each number of workgroups per CU, and
+        // the cheapest of those.
+        const int longest = max(max(split, (int)units_cap), a.max_split_blocks / kOneGenerationStretch);
+        const int step = (longest - lo + 63) / 63;
+        const int lane = tid & 63, cand = min(lo + lane * step, longest);
+        // pieces of a row by a reciprocal (halfway between the quotients'
+        // steps: exact below 2^18 blocks, and near enough above)
+        const float inv = 1.0f / (float)cand, half = (float)cand - 0.5f;
+        int mine = 0;
+        for (int r = tid >> 6; r < B; r += kPlanWaves) mine += (int)(((float)row_np[r] + half) * inv);
+        pieces[tid >> 6][lane] = mine;
+        __syncthreads();
+        int64_t n = 0;
 #pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) n += __shfl_xor(n, off);
-            if ((tid & 63) == 0) wsum_l[tid >> 6] = (int64_t)n * a.waves_per_desc;
-            __syncthreads();
-            int w = 0;
-            while (w < kPlanWaves - 1 && wsum_l[w] > a.wave_slots) ++w;
-            const bool fits = wsum_l[w] <= a.wave_slots;
-            __syncthreads();
-            if (!fits) break;   // several generations: the default length
-            split = min(lo + w * step, hi);
-            if (w == 0 || step <= 1) break;
-            hi = split;
-            lo = hi - step + 1;
+        for (int w = 0; w < kPlanWaves; ++w) n += pieces[w][lane];
+        n *= a.waves_per_desc;
+        int best = 0x7fffffff;
+        if (__ballot(n <= a.wave_slots)) {   // (the counts fall with the length)
+#pragma unroll
+            for (int per_cu = 1; per_cu <= kDecodeWavesPerCu / kWavesPerGroup; ++per_cu) {
+                const uint64_t fit = __ballot(n <= a.wave_slots / kDecodeWavesPerCu * (per_cu * kWavesPerGroup));
+                if (!fit) continue;
+                const int len = min(lo + (__ffsll((unsigned long long)fit) - 1) * step, longest);
+                const int cost = decode_cost(per_cu, len, a.light_steps != 0);
+                if (10 * (int64_t)cost < 9 * (int64_t)best) {
+                    best = cost;
+                    split = len;
+                }
+            }
         }
     }
 

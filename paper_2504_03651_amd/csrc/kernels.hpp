@@ -91,6 +91,7 @@ struct DevPlanArgs {
     int32_t split_blocks;           // decode piece of the descriptor region's bound
     int32_t min_split_blocks, max_split_blocks;   // shortest and longest piece of the rule
     int32_t wave_slots;             // decode waves the chip keeps resident
+    int32_t light_steps;            // decode_cost's `light`
     int32_t waves_per_desc;         // num_kv_heads * head_chunks
     int32_t tile_tokens;            // tokens per prefill tile
     int32_t slots_per_desc;         // partial slots per decode piece (one token)

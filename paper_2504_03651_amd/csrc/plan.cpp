@@ -152,22 +152,32 @@ int build_plan(const HostBatch &b, int32_t Hkv, int32_t Hq, int32_t D, const Pla
         return n * plan.waves_per_desc;
     };
     // A launch that fits one generation of resident waves starts every wave
-    // at once and has no partly filled last generation: take the shortest
-    // pieces, from kMinSplitBlocks up to kOneGenerationStretch times the
-    // default (and no longer than the unit target allows), that bring the
-    // launch under that.  Short of it the launch leaves slots empty, and a CU
-    // that holds three workgroups beside CUs that hold two ends the kernel.
+    // at once and has no partly filled last generation.  If pieces no longer
+    // than kOneGenerationStretch times the default (nor than the unit target
+    // allows) bring the launch under that, take the shortest pieces that leave
+    // at most one, two or three workgroups to a CU, whichever of the three
+    // ends first (decode_cost).
     const int64_t slots = (int64_t)kDecodeWavesPerCu * opt.num_cus;
     const int32_t longest = (int32_t)std::max<int64_t>(
         split, std::min<int64_t>((int64_t)kOneGenerationStretch * opt.split_blocks, units_cap));
     if (waves_for(longest) <= slots) {
-        int32_t lo = min_split, hi = longest;
-        while (lo < hi) {
-            const int32_t mid = lo + (hi - lo) / 2;
-            if (waves_for(mid) <= slots) hi = mid;
-            else lo = mid + 1;
+        int32_t best = INT32_MAX;
+        int32_t hi = std::max(longest, opt.split_blocks);
+        for (int32_t per_cu = 1; per_cu <= kDecodeWavesPerCu / kWavesPerGroup; ++per_cu) {
+            const int64_t most = (int64_t)per_cu * kWavesPerGroup * opt.num_cus;
+            if (waves_for(hi) > most) continue;
+            int32_t lo = min_split;
+            while (lo < hi) {
+                const int32_t mid = lo + (hi - lo) / 2;
+                if (waves_for(mid) <= most) hi = mid;
+                else lo = mid + 1;
+            }
+            const int32_t cost = decode_cost(per_cu, hi, opt.light);
+            if (10 * (int64_t)cost < 9 * (int64_t)best) {
+                best = cost;
+                split = hi;
+            }
         }
-        split = lo;
     }
 
     // contributions per decode row: sum over its segments of their splits

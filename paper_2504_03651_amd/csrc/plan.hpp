@@ -69,7 +69,7 @@ constexpr int kPrefillMinChainTiles = 2;  // fewest 64-key tiles moved to a chai
 // the bytes per block (a sweep of 16-128 blocks on the decode-only, mixed and
 // e4m3 batches).
 constexpr int64_t kSplitBytes = 384 * 1024;
-constexpr int kMinSplitBlocks = 8;        // shortest decode piece on small batches
+constexpr int kMinSplitBlocks = 6;        // shortest decode piece on small batches
 constexpr int kSplitTargetUnits = 2048;   // decode units below which pieces shrink
 #ifndef ECHO_EQ_GENS
 #define ECHO_EQ_GENS 3
@@ -92,6 +92,20 @@ constexpr int kDecodeWavesPerCu = 12;
 // one at 128, decode 0.442 -> 0.386 ms; batches that cannot get there keep
 // the default)
 constexpr int kOneGenerationStretch = ECHO_ONE_GEN_STRETCH;
+
+// Relative time of a decode launch of one generation whose fullest CU holds
+// per_cu workgroups (1-3), each walking pieces of `blocks` blocks two at a time.
+// A step takes about 2.6, 4.3 and 6.2 us with one, two and three workgroups on
+// the CU (bf16 at head_dim 128, measured at 4 and 3 steps on 8 rows, and at 24
+// steps with all CUs full); half the bytes per step leave room for a second
+// workgroup at little cost.
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+constexpr int32_t decode_cost(int32_t per_cu, int32_t blocks, bool light) {
+    constexpr int32_t step[2][3] = {{28, 43, 62}, {28, 30, 44}};
+    return step[light ? 1 : 0][per_cu - 1] * ((blocks + 1) / 2);
+}
 
 // Merge entries of a token from which its heads get a wave each: past 16 a
 // 16-lane group would walk them in several turns, a chain of loads each.
@@ -139,6 +153,7 @@ struct HostBatch {
 
 struct PlanOptions {
     int split_blocks = 48;  // key blocks per decode split (set from kSplitBytes)
+    bool light = false;     // decode steps of half the bytes (e4m3, or head_dim 64)
     int num_cus = 256;      // compute units: prefill key ranges are cut into
                             // pieces when workgroups would fill at most half of them
 };
