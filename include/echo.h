@@ -138,13 +138,14 @@ int echo_kv_append(const echo_kv_pool_t *pool, const echo_batch_t *batch, const 
  *     host_workspace -- pinned host memory the device reads coherently
  *     (hipHostMalloc with hipHostMallocMapped | hipHostMallocCoherent), at
  *     least echo_attn_host_workspace_bytes() bytes, 16-byte aligned -- and
- *     copied into `workspace` by a kernel on `stream`.  The call does not
- *     wait for that copy: the caller must not change or reuse host_workspace
- *     until this call's work on `stream` has run past it (for example, wait
- *     on an event recorded after the call, or rotate several buffers).
+ *     read there by the call's kernels on `stream`, which copy it into
+ *     `workspace` or read it in place.  The call does not wait for them: the
+ *     caller must not change or reuse host_workspace until this call's work on
+ *     `stream` has completed (for example, wait on an event recorded after
+ *     the call, or rotate several buffers).
  *     Memory that is not pinned host memory returns ECHO_E_WORKSPACE;
- *   - without mirrors, host_workspace is ignored (may be NULL) and two small
- *     kernels build the plan in `workspace` from the device metadata: no
+ *   - without mirrors, host_workspace is ignored (may be NULL) and one or two
+ *     small kernels build the plan in `workspace` from the device metadata: no
  *     prefix grouping (shared blocks are read once per row), decode rows cut
  *     into equal key pieces, prefill rows into tiles, grids sized from the
  *     scalar fields.  The results are the same within rounding.  Rows whose
@@ -263,8 +264,9 @@ int echo_validate(const echo_kv_pool_t *pool, const echo_batch_t *batch, int32_t
  * plan upload and each kernel launch.  Recording is off unless enabled with
  * echo_profile(1) on the same thread; kernels not launched report 0. */
 typedef struct {
-    float upload_ms;    /* plan upload from the host workspace, or the two device
-                           planning kernels when there are no host mirrors */
+    float upload_ms;    /* plan upload from the host workspace (0 when the decode
+                           kernel reads it in place), or device planning when
+                           there are no host mirrors */
     float prefill_ms;   /* prefill_kernel: chunked-prefill tiles */
     float decode_ms;    /* attn_kernel: decode split-KV / shared-prefix items */
     float merge_ms;     /* merge_kernel: log-sum-exp merge of partial results */

@@ -369,6 +369,13 @@ struct AttnLaunch {
     int32_t n_pdesc_grid = 0;     // prefill descriptors that get workgroups (a capacity with counts)
     int32_t head_chunks = 1, heads_per_chunk = 1, waves_per_desc = 1, run_log2 = 0,
             pf_max_blocks = 0, num_cus = 256;
+    // The decode kernel reads its part of the plan where the host packed it and
+    // copies copy_words of it to the workspace for the kernels after it: it then
+    // goes first, and no upload kernel before it
+    const uint32_t *copy_src = nullptr;
+    uint32_t *copy_dst = nullptr;
+    int64_t copy_words = 0;
+    bool direct = false;
 };
 
 int launch_attention(const echo_kv_pool_t *pool, const echo_batch_t *batch, const void *q,
@@ -398,6 +405,10 @@ int launch_attention(const echo_kv_pool_t *pool, const echo_batch_t *batch, cons
     a.part_o = w.part_o;
     a.part_lse = w.part_lse;
     a.counts = w.counts;
+    a.copy_src = w.copy_src;
+    a.copy_dst = w.copy_dst;
+    a.copy_words = w.copy_words;
+    a.copy_first = 0;
     MergeArgs m;
     m.n_rows = w.n_merge_rows;
     m.n_wide = w.n_merge_wide;
@@ -441,26 +452,32 @@ int launch_attention(const echo_kv_pool_t *pool, const echo_batch_t *batch, cons
     const int D = pool->head_dim;
     const bool fp8 = pool->dtype == ECHO_KV_FP8_E4M3;
     hipError_t e;
-    // prefill, decode and merge in that order on the caller's stream; with
-    // profiling on, an event pair around each kernel that launches (an empty
-    // pair still costs GPU time between the two records)
-    if (pf.n_logical > 0) {
+    // prefill and decode, then merge, on the caller's stream; with profiling
+    // on, an event pair around each kernel that launches (an empty pair still
+    // costs GPU time between the two records)
+    auto prefill = [&]() -> int {
+        if (pf.n_logical <= 0) return ECHO_OK;
         if (ev && (e = hipEventRecord(ev[2], s)) != hipSuccess) return hip_fail(e, "hipEventRecord");
-        if ((e = launch_prefill(pf, D, fp8, w.num_cus, s)) != hipSuccess) return hip_fail(e, "prefill launch");
+        if ((e = launch_prefill(pf, D, fp8, w.num_cus, s)) != hipSuccess)
+            return hip_fail(e, "prefill launch");
         if (ev && (e = hipEventRecord(ev[3], s)) != hipSuccess) return hip_fail(e, "hipEventRecord");
-    }
+        return ECHO_OK;
+    };
+    int rc;
+    if (!w.direct && (rc = prefill())) return rc;
     if (a.n_waves > 0) {
         if (ev && (e = hipEventRecord(ev[4], s)) != hipSuccess) return hip_fail(e, "hipEventRecord");
         if ((e = launch_decode(a, D, fp8, s)) != hipSuccess) return hip_fail(e, "decode launch");
         if (ev && (e = hipEventRecord(ev[5], s)) != hipSuccess) return hip_fail(e, "hipEventRecord");
     }
+    if (w.direct && (rc = prefill())) return rc;
     if (m.n_rows > 0) {
         if (ev && (e = hipEventRecord(ev[6], s)) != hipSuccess) return hip_fail(e, "hipEventRecord");
         if ((e = launch_merge(m, D, s)) != hipSuccess) return hip_fail(e, "merge launch");
         if (ev && (e = hipEventRecord(ev[7], s)) != hipSuccess) return hip_fail(e, "hipEventRecord");
     }
     g_prof.valid = ev != nullptr;
-    g_prof.launched[0] = true;
+    g_prof.launched[0] = !w.direct;
     g_prof.launched[1] = pf.n_logical > 0;
     g_prof.launched[2] = a.n_waves > 0;
     g_prof.launched[3] = m.n_rows > 0;
@@ -568,17 +585,32 @@ int attn_planned(const echo_kv_pool_t *pool, const echo_batch_t *batch, const vo
     // every check is done: pack the plan into the host workspace and enqueue
     pack_plan(plan, host_workspace);
     hipError_t e;
-    if (ev && (e = hipEventRecord(ev[0], s)) != hipSuccess) return hip_fail(e, "hipEventRecord");
-    if ((e = launch_plan_upload(staged, workspace, L.upload_words, s)) != hipSuccess)
-        return hip_fail(e, "plan upload launch");
-    if (ev && (e = hipEventRecord(ev[1], s)) != hipSuccess) return hip_fail(e, "hipEventRecord");
+    // A decode launch of one generation reads its descriptors over the host
+    // link, which every wave waits for once (1.4 us), instead of waiting for a
+    // copy kernel (3.3 us and the gap after it): 8 rows 33.4 -> 30.8 us a call
+    // and append.  Launches of several generations would wait in each.
+    const bool direct = L.n_desc > 0 && L.n_desc * plan.waves_per_desc <=
+                                            (int64_t)kDecodeWavesPerCu * plan_options(pool).num_cus;
+    if (!direct) {
+        if (ev && (e = hipEventRecord(ev[0], s)) != hipSuccess) return hip_fail(e, "hipEventRecord");
+        if ((e = launch_plan_upload(staged, workspace, L.upload_words, s)) != hipSuccess)
+            return hip_fail(e, "plan upload launch");
+        if (ev && (e = hipEventRecord(ev[1], s)) != hipSuccess) return hip_fail(e, "hipEventRecord");
+    }
 
     int32_t *w = (int32_t *)workspace;
+    const int32_t *dec = direct ? (const int32_t *)staged : w;   // the decode kernel's part
     AttnLaunch a;
-    a.desc = (const WorkDesc *)(w + L.off_desc);
+    a.direct = direct;
+    if (direct && (L.n_merge_rows > 0 || L.n_pdesc > 0)) {
+        a.copy_src = (const uint32_t *)staged;
+        a.copy_dst = (uint32_t *)workspace;
+        a.copy_words = L.upload_words;
+    }
+    a.desc = (const WorkDesc *)(dec + L.off_desc);
     a.pdesc = (const PrefillDesc *)(w + L.off_pdesc);
-    a.tok_list = w + L.off_tok_list;
-    a.klim = w + L.off_klim;
+    a.tok_list = dec + L.off_tok_list;
+    a.klim = dec + L.off_klim;
     a.merge_tok = w + L.off_merge_tok;
     a.merge_ptr = w + L.off_merge_ptr;
     a.merge_ent = w + L.off_merge_ent;

@@ -722,8 +722,25 @@ __device__ __forceinline__ void decode_body(const AttnArgs &a, int P, int tid) {
     for (int i = 0; i < NT; ++i) *(f32x4_t *)(dst + 16 * i + 4 * g4) = acc[i] * inv;
 }
 
+// `words` 32-bit words by workgroups of 256 threads, 16 bytes per thread and
+// step; part of `parts`
+__device__ __forceinline__ void copy_words(const uint32_t *__restrict__ src, uint32_t *__restrict__ dst,
+                                           int64_t words, int part, int parts) {
+    const int64_t n16 = words / 4;
+    const int64_t stride = (int64_t)parts * 256;
+    for (int64_t i = (int64_t)part * 256 + threadIdx.x; i < n16; i += stride)
+        ((u32x4_t *)dst)[i] = ((const u32x4_t *)src)[i];
+    const int64_t t = 4 * n16 + threadIdx.x;
+    if (part == 0 && t < words) dst[t] = src[t];
+}
+
 template <int D, bool FP8>
 __global__ __launch_bounds__(256) void attn_kernel(AttnArgs a) {
+    if ((int)blockIdx.x >= a.copy_first) {
+        copy_words(a.copy_src, a.copy_dst, a.copy_words, blockIdx.x - a.copy_first,
+                   gridDim.x - a.copy_first);
+        return;
+    }
     decode_body<D, FP8>(a, blockIdx.x, threadIdx.x);
 }
 
@@ -1747,15 +1764,10 @@ hipError_t scratch_region(void **ptr) {
 //
 // Copies the packed plan from pinned, coherent host memory into the
 // workspace.  A kernel on the stream avoids the copy engine's hand-off with
-// the kernels around it; each thread moves 16 bytes per step.
+// the kernels around it.
 __global__ __launch_bounds__(256) void plan_upload_kernel(const uint32_t *__restrict__ src,
                                                           uint32_t *__restrict__ dst, int64_t words) {
-    const int64_t n16 = words / 4;
-    const int64_t stride = (int64_t)gridDim.x * 256;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n16; i += stride)
-        ((u32x4_t *)dst)[i] = ((const u32x4_t *)src)[i];
-    const int64_t t = 4 * n16 + (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (blockIdx.x == 0 && t < words) dst[t] = src[t];
+    copy_words(src, dst, words, blockIdx.x, gridDim.x);
 }
 
 // ------------------------------------------------------------------ launchers
@@ -1866,7 +1878,10 @@ static int64_t decode_grid(AttnArgs &b) {
 hipError_t launch_decode(const AttnArgs &a, int head_dim, bool fp8, hipStream_t s) {
     if (a.n_waves <= 0) return hipSuccess;
     AttnArgs b = a;
-    const dim3 grid((unsigned)decode_grid(b)), block(256);
+    const int64_t wgs = decode_grid(b);
+    b.copy_first = (int32_t)wgs;
+    const int64_t copies = std::min<int64_t>((a.copy_words + 1023) / 1024, 16);
+    const dim3 grid((unsigned)(wgs + copies)), block(256);
     if (head_dim == 64 && !fp8) hipLaunchKernelGGL((attn_kernel<64, false>), grid, block, 0, s, b);
     else if (head_dim == 64) hipLaunchKernelGGL((attn_kernel<64, true>), grid, block, 0, s, b);
     else if (!fp8) hipLaunchKernelGGL((attn_kernel<128, false>), grid, block, 0, s, b);

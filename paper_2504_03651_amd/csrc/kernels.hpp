@@ -43,6 +43,12 @@ struct AttnArgs {
     int32_t run_log2;               // XCD run length: the caller's minimum, set by the launcher
     const int32_t *counts;          // device-built plan: its header (word 0 = descriptors);
                                     // NULL when n_waves is exact
+    // plan read from host memory: copied to the workspace by workgroups past the
+    // decode grid, for the kernels that follow
+    const uint32_t *copy_src;
+    uint32_t *copy_dst;
+    int64_t copy_words;             // 0: nothing to copy
+    int32_t copy_first;             // first such workgroup, set by the launcher
 };
 
 struct PrefillArgs {

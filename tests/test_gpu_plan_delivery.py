@@ -1,0 +1,73 @@
+"""How a host-built plan reaches the kernels: the decode kernel of a launch of
+one generation of waves reads it in pinned host memory and copies it for the
+kernels after it; larger launches copy it first.  Both sides of that rule (3,072
+waves on 256 CUs), with and without chunks and merges, against the oracle; and a
+captured call replayed with other work in between, against the eager result."""
+import ctypes
+
+import pytest
+
+import oracle
+from paper_2504_03651_amd import workload as W
+from tests.gpu_util import ATOL, attn_error, say
+
+pytestmark = pytest.mark.gpu
+
+CHUNK = [W.RowSpec(W.PREFILL, 100, 70)]
+CASES = {
+    # 32 KV heads: 96 rows of one piece are 3,072 waves
+    "direct": [W.RowSpec(W.DECODE, 20 + i % 60, 1) for i in range(96)],
+    "copied": [W.RowSpec(W.DECODE, 20 + i % 60, 1) for i in range(97)],
+    "direct-chunk": [W.RowSpec(W.DECODE, 20 + i, 1) for i in range(40)] + CHUNK,
+    "copied-chunk": [W.RowSpec(W.DECODE, 20 + i, 1) for i in range(97)] + CHUNK,
+    "direct-merge": [W.RowSpec(W.DECODE, 900 + 90 * i, 1) for i in range(4)] + CHUNK,
+    "chunk-only": CHUNK,
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_plan_delivery(name):
+    import torch
+    from paper_2504_03651_amd.session import Iteration
+    w = W.build(name, CASES[name], {}, 32, 32, 64, seed=101)
+    say(f"[case] plan delivery {name}: rows={w.batch.num_rows}")
+    it = Iteration(w)
+    for _ in range(6):                    # round the ring of host buffers and past it
+        it.out.fill_(float("nan"))
+        it.step()
+    torch.cuda.synchronize()
+    _, ref = oracle.run_iteration(w)
+    err, _ = attn_error(it.out.cpu().numpy().reshape(ref.shape), ref)
+    say(f"       max abs err {err:.3e}")
+    assert err <= ATOL
+
+
+@pytest.mark.parametrize("name", ["direct-merge", "copied-chunk"])
+def test_captured_call_replays(name):
+    import torch
+    from paper_2504_03651_amd import echo
+    from paper_2504_03651_amd.session import Iteration
+    w = W.build(name, CASES[name], {}, 32, 32, 64, seed=103)
+    say(f"[case] captured {name}")
+    it = Iteration(w)
+    it.step()
+    torch.cuda.synchronize()
+    want = it.out.clone()
+    hw = echo.HostWorkspace(slots=1)
+    ptr, size, _ = hw.acquire(echo.host_workspace_bytes(it.pool, it.batch, 32))
+    cp, cb = it.pool.c(), it.batch.c()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        rc = echo.lib().echo_attn_mixed(
+            ctypes.byref(cp), ctypes.byref(cb), it.q.data_ptr(), 32, w.sm_scale, it.out.data_ptr(),
+            it.workspace.data_ptr(), it.workspace.numel(), ptr, size,
+            ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == echo.ECHO_OK, echo.last_error()
+    for _ in range(4):
+        it.out.fill_(float("nan"))
+        it.workspace.fill_(0x5A)          # other work between the replays
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(it.out.view(torch.int32), want.view(torch.int32))
+    hw.close()
