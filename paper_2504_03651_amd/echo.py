@@ -270,10 +270,13 @@ class HostWorkspace:
         self._spare = [None] * slots      # events that have been waited for, to record again
         self._next = 0
 
-    def acquire(self, nbytes: int):
-        """(pointer, size, slot) of a buffer of at least ``nbytes`` bytes."""
-        i = self._next
-        self._next = (i + 1) % len(self._bufs)
+    def acquire(self, nbytes: int, slot=None):
+        """(pointer, size, slot) of a buffer of at least ``nbytes`` bytes: the
+        ring's next one, or the one of ``slot``, acquired before and not used."""
+        i = slot
+        if i is None:
+            i = self._next
+            self._next = (i + 1) % len(self._bufs)
         ev = self._events[i]
         if ev is not None:
             ev.synchronize()
@@ -353,7 +356,8 @@ def attn_mixed(pool: KVPool, batch: DeviceBatch, q, num_q_heads: int, sm_scale: 
         return
     # The size of a plan is known once it is made, so the call gets the ring's
     # next buffer as it is; only a plan that does not fit it (the call has then
-    # enqueued nothing) asks for the size, which plans once more.
+    # enqueued nothing) asks for the size, which plans once more.  The same
+    # buffer grows then, so that each of the ring's does so once.
     hw = host_workspace or default_host_workspace()
     hptr, hsize, slot = hw.acquire(1)
     code = call(hptr, hsize)
@@ -362,7 +366,7 @@ def attn_mixed(pool: KVPool, batch: DeviceBatch, q, num_q_heads: int, sm_scale: 
         need = host_workspace_bytes(pool, batch, num_q_heads)
         if need <= hsize:
             raise EchoError(code, "echo_attn_mixed", detail)
-        hptr, hsize, slot = hw.acquire(need)
+        hptr, hsize, slot = hw.acquire(need, slot)
         code = call(hptr, hsize)
     _check(code, "echo_attn_mixed")
     hw.release(slot, s)

@@ -4,6 +4,7 @@ import copy
 import ctypes
 
 import numpy as np
+import torch
 
 from paper_2504_03651_amd import echo
 from paper_2504_03651_amd import workload as W
@@ -42,3 +43,44 @@ def test_block_copy_pairs_are_checked_in_any_order():
                 [(1, 5), (2, 6), (7, 1)], [(1, 5), (2, 6), (6, 8), (9, 5)]):
         assert call(bad) == echo.ECHO_E_INVALID, bad
     assert call([(1, 64)]) == echo.ECHO_E_RANGE and call([(-1, 3)]) == echo.ECHO_E_RANGE
+
+
+def test_each_buffer_of_the_ring_grows_once(monkeypatch):
+    # a plan larger than a new buffer: the first use of each buffer is refused
+    # and grows it, and from then on every call plans once
+    need, calls, kept = 100_000, [], []
+
+    class Lib:
+        def hipHostMalloc(self, p, size, flags):
+            kept.append(ctypes.create_string_buffer(size.value))
+            ctypes.cast(p, ctypes.POINTER(ctypes.c_void_p))[0] = ctypes.addressof(kept[-1])
+            return 0
+
+        def hipHostFree(self, p):
+            return 0
+
+        def echo_attn_host_workspace_bytes(self, *a):
+            return need
+
+        def echo_attn_mixed(self, *a):
+            calls.append(a[8])
+            return echo.ECHO_OK if a[9] >= need else echo.ECHO_E_WORKSPACE
+
+        def echo_last_error(self):
+            return b""
+
+    class Stream:
+        cuda_stream = 0
+
+    fake = Lib()
+    monkeypatch.setattr(echo, "lib", lambda: fake)
+    w = W.config1()
+    pool = echo.KVPool(w.num_blocks, w.num_kv_heads, w.head_dim, False, "cpu")
+    b = echo.DeviceBatch(w.batch, "cpu")
+    t = torch.zeros(4)
+    hw = echo.HostWorkspace()
+    monkeypatch.setattr(hw, "release", lambda slot, stream: None)
+    for i in range(12):
+        before = len(calls)
+        echo.attn_mixed(pool, b, t, w.num_q_heads, 1.0, t, t, Stream(), hw)
+        assert len(calls) - before == (2 if i < 4 else 1), i
