@@ -4,6 +4,7 @@ import copy
 import ctypes
 
 import numpy as np
+import pytest
 import torch
 
 from paper_2504_03651_amd import echo
@@ -30,10 +31,11 @@ def test_mirror_addresses_follow_the_arrays():
     assert _addresses(b) == (None,) * 4
 
 
-def test_block_copy_pairs_are_checked_in_any_order():
+@pytest.mark.parametrize("blocks", [64, (1 << 20) + 1, 2 ** 31 - 1])
+def test_block_copy_pairs_are_checked_in_any_order(blocks):
     # one pass over the pairs finds what sorting found: a destination twice, a
-    # block on both sides in either order, and accepts a source used twice
-    pool = echo.CPool(0x1000, 0x1000, None, None, 64, 2, 64, 16, echo.KV_BF16)
+    # block on both sides in either order; pools of many blocks are sorted
+    pool = echo.CPool(0x1000, 0x1000, None, None, blocks, 2, 64, 16, echo.KV_BF16)
 
     def call(pairs):
         h = np.ascontiguousarray(pairs, np.int32)
@@ -42,7 +44,9 @@ def test_block_copy_pairs_are_checked_in_any_order():
     for bad in ([(1, 5), (2, 5)], [(1, 5), (5, 6)], [(5, 6), (1, 5)], [(3, 3)],
                 [(1, 5), (2, 6), (7, 1)], [(1, 5), (2, 6), (6, 8), (9, 5)]):
         assert call(bad) == echo.ECHO_E_INVALID, bad
-    assert call([(1, 64)]) == echo.ECHO_E_RANGE and call([(-1, 3)]) == echo.ECHO_E_RANGE
+    assert call([(-1, 3)]) == echo.ECHO_E_RANGE
+    if blocks < 2 ** 31 - 1:
+        assert call([(1, blocks)]) == echo.ECHO_E_RANGE
 
 
 def test_each_buffer_of_the_ring_grows_once(monkeypatch):
