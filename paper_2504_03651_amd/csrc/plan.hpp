@@ -70,6 +70,10 @@ constexpr int kPrefillMinChainTiles = 2;  // fewest 64-key tiles moved to a chai
 // e4m3 batches).
 constexpr int64_t kSplitBytes = 384 * 1024;
 constexpr int kMinSplitBlocks = 6;        // shortest decode piece on small batches
+// Shortest piece that a device-built plan's regions are sized for: at 6 blocks
+// batches that fit the static entry point's scratch at 8 would outgrow it.  Pieces
+// are shorter where the batch's lengths leave room for them.
+constexpr int kMinRegionSplitBlocks = 8;
 constexpr int kSplitTargetUnits = 2048;   // decode units below which pieces shrink
 #ifndef ECHO_EQ_GENS
 #define ECHO_EQ_GENS 3

@@ -88,3 +88,12 @@ def test_each_buffer_of_the_ring_grows_once(monkeypatch):
         before = len(calls)
         echo.attn_mixed(pool, b, t, w.num_q_heads, 1.0, t, t, Stream(), hw)
         assert len(calls) - before == (2 if i < 4 else 1), i
+
+
+def test_device_plan_regions_fit_the_static_scratch():
+    # 2,040 rows of at most 7 blocks and 16 heads: regions for pieces of 6 blocks
+    # (two a row) would outgrow the static entry point's 32 MiB
+    pool = echo.CPool(0x1000, 0x1000, None, None, 20000, 1, 128, 16, echo.KV_BF16)
+    b = echo.CBatch(2040, 7, 2040, 1, 112, 0x1000, 0x1000, 0x1000, 0x1000)
+    n = echo.lib().echo_attn_workspace_bytes(ctypes.byref(pool), ctypes.byref(b), 16)
+    assert 0 < n <= 32 << 20
