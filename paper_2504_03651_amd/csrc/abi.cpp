@@ -588,9 +588,14 @@ int attn_planned(const echo_kv_pool_t *pool, const echo_batch_t *batch, const vo
     // A decode launch of one generation reads its descriptors over the host
     // link, which every wave waits for once (1.4 us), instead of waiting for a
     // copy kernel (3.3 us and the gap after it): 8 rows 33.4 -> 30.8 us a call
-    // and append.  Launches of several generations would wait in each.
-    const bool direct = L.n_desc > 0 && L.n_desc * plan.waves_per_desc <=
-                                            (int64_t)kDecodeWavesPerCu * plan_options(pool).num_cus;
+    // and append.  Launches of several generations would wait in each.  Nor
+    // where the prefill takes more than two rounds of CUs and 3 us are nothing:
+    // the decode kernel is better off behind it (28 rows of 32,768 keys shared
+    // with four chunks: 434 us first, 367 us behind; the pass 0.6-1.1% slower).
+    const int32_t num_cus = plan_options(pool).num_cus;
+    const bool direct =
+        L.n_desc > 0 && L.n_desc * plan.waves_per_desc <= (int64_t)kDecodeWavesPerCu * num_cus &&
+        (int64_t)plan.pdesc_grid * pool->num_kv_heads <= 2 * (int64_t)num_cus;
     if (!direct) {
         if (ev && (e = hipEventRecord(ev[0], s)) != hipSuccess) return hip_fail(e, "hipEventRecord");
         if ((e = launch_plan_upload(staged, workspace, L.upload_words, s)) != hipSuccess)

@@ -1,8 +1,9 @@
 """How a host-built plan reaches the kernels: the decode kernel of a launch of
 one generation of waves reads it in pinned host memory and copies it for the
-kernels after it; larger launches copy it first.  Both sides of that rule (3,072
-waves on 256 CUs), with and without chunks and merges, against the oracle; and a
-captured call replayed with other work in between, against the eager result."""
+kernels after it; larger launches, and those beside a large prefill, copy it
+first.  Both sides of that rule (3,072 waves, 512 prefill workgroups on 256
+CUs), with and without chunks and merges, against the oracle; and a captured
+call replayed with other work in between, against the eager result."""
 import ctypes
 
 import pytest
@@ -22,6 +23,9 @@ CASES = {
     "copied-chunk": [W.RowSpec(W.DECODE, 20 + i, 1) for i in range(97)] + CHUNK,
     "direct-merge": [W.RowSpec(W.DECODE, 900 + 90 * i, 1) for i in range(4)] + CHUNK,
     "chunk-only": CHUNK,
+    # a chunk is one tile: 512 prefill workgroups (two rounds of CUs), and 544
+    "direct-two-rounds": [W.RowSpec(W.DECODE, 900, 1)] + 16 * CHUNK,
+    "copied-past-them": [W.RowSpec(W.DECODE, 900, 1)] + 17 * CHUNK,
 }
 
 
