@@ -322,9 +322,9 @@ int dev_layout(const echo_kv_pool_t *pool, const echo_batch_t *b, int32_t Hq, De
     // longest length the scalars allow
     const PlanOptions o = plan_options(pool);
     const int64_t seg_blocks = B * (((int64_t)b->max_seq_len + kBlock - 1) / kBlock);
-    L.min_split = std::min(kMinSplitBlocks, std::max(2, o.split_blocks));
+    L.min_split = std::min(kMinOneGenSplitBlocks, std::max(2, o.split_blocks));
     L.split_blocks = (int32_t)std::max<int64_t>(
-        std::min(kMinRegionSplitBlocks, std::max(2, o.split_blocks)),
+        std::min(kMinSplitBlocks, std::max(2, o.split_blocks)),
         std::min<int64_t>(o.split_blocks, seg_blocks * Hkv * L.head_chunks / kSplitTargetUnits));
     L.max_split = kOneGenerationStretch * o.split_blocks;
     L.wave_slots = kDecodeWavesPerCu * o.num_cus;

@@ -1574,7 +1574,8 @@ __global__ __launch_bounds__(kPlanThreads) void dev_plan_kernel(DevPlanArgs a) {
     // Pieces of decode rows: the host planner's rule (build_plan) on the blocks
     // there are, but no shorter than the descriptor region allows.  The region
     // holds every row cut into pieces of split_blocks, the rule's value for
-    // the longest lengths the scalars allow.
+    // the longest lengths the scalars allow.  (The merge is launched in any case,
+    // so the rule's price of a merge has no place here.)
     auto dec_blocks = [&]() -> int { return ok && q == 1 ? (L + 15) / 16 : 0; };
     int64_t blocks = 0;
     {
@@ -1596,7 +1597,7 @@ __global__ __launch_bounds__(kPlanThreads) void dev_plan_kernel(DevPlanArgs a) {
     int lo = a.split_blocks;                            // shortest piece that fits the region
     if (room > 0 && blocks < ((int64_t)1 << 31))
         lo = min(lo, max(a.min_split_blocks, (int)(((uint32_t)blocks + room - 1) / room)));
-    int split = min(a.split_blocks, max(lo, (int)units_cap));
+    int split = min(a.split_blocks, max(max(lo, kMinSplitBlocks), (int)units_cap));
     if (B <= kPlanThreads) {
         // Waves of the launch for 64 piece lengths from lo to the longest, one
         // per lane (the waves take the rows in turn); then, as the host planner

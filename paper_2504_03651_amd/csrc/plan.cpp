@@ -134,6 +134,14 @@ int build_plan(const HostBatch &b, int32_t Hkv, int32_t Hq, int32_t D, const Pla
         segs.push_back(s);
     }
 
+    // Prefill tiles of at most one round of CUs may have their keys cut (below).
+    const int32_t bt_tok = std::max(1, kPrefillQueries / G);
+    int64_t pf_tiles = 0;
+    for (int32_t r = 0; r < B; ++r)
+        if (b.kind[r] == ECHO_ROW_PREFILL)
+            pf_tiles += (b.q_start[r + 1] - b.q_start[r] + bt_tok - 1) / bt_tok;
+    const bool prefill_may_be_cut = pf_tiles > 0 && pf_tiles * Hkv <= (int64_t)opt.num_cus;
+
     // Key ranges are split into pieces of `split` blocks.  Long pieces keep
     // the partial results and the merge small; on a small decode batch they
     // would leave most of the GPU idle while a few waves walk long ranges one
@@ -142,9 +150,10 @@ int build_plan(const HostBatch &b, int32_t Hkv, int32_t Hq, int32_t D, const Pla
     // (piece, KV head, head chunk) units.
     int64_t seg_blocks = 0;
     for (const Segment &s : segs) seg_blocks += s.j1 - s.j0;
-    const int32_t min_split = std::min<int32_t>(kMinSplitBlocks, std::max(2, opt.split_blocks));
     const int64_t units_cap = seg_blocks * Hkv * nhc / kSplitTargetUnits;
-    int32_t split = (int32_t)std::max<int64_t>(min_split, std::min<int64_t>(opt.split_blocks, units_cap));
+    int32_t split = (int32_t)std::max<int64_t>(
+        std::min<int32_t>(kMinSplitBlocks, std::max(2, opt.split_blocks)),
+        std::min<int64_t>(opt.split_blocks, units_cap));
     auto waves_for = [&](int32_t sp) {
         int64_t n = 0;
         for (const Segment &s : segs)
@@ -152,31 +161,49 @@ int build_plan(const HostBatch &b, int32_t Hkv, int32_t Hq, int32_t D, const Pla
         return n * plan.waves_per_desc;
     };
     // A launch that fits one generation of resident waves starts every wave
-    // at once and has no partly filled last generation.  If pieces no longer
-    // than kOneGenerationStretch times the default (nor than the unit target
-    // allows) bring the launch under that, take the shortest pieces that leave
-    // at most one, two or three workgroups to a CU, whichever of the three
-    // ends first (decode_cost).
+    // at once and has no partly filled last generation.  If pieces up to
+    // kOneGenerationStretch times the default (as far as the unit target allows)
+    // bring the launch under that, take the shortest pieces that leave at most
+    // one, two or three workgroups to a CU, whichever of the three ends first
+    // (decode_cost).  Longer pieces than the unit target's, up to the default, are
+    // taken where that beats the generations that the target's pieces fill: 200
+    // rows of 9 blocks (GQA 32/8) whole, in 1,600 waves, 26 us, cut 36 us; 40
+    // shared runs of 43 blocks beside 238 tails of 6 (e4m3) in 1.5 generations of
+    // 12-block pieces 48 us, in one with the runs whole 61 us.
     const int64_t slots = (int64_t)kDecodeWavesPerCu * opt.num_cus;
-    const int32_t longest = (int32_t)std::max<int64_t>(
+    const int32_t target_longest = (int32_t)std::max<int64_t>(
         split, std::min<int64_t>((int64_t)kOneGenerationStretch * opt.split_blocks, units_cap));
+    const int32_t longest = std::max(target_longest, opt.split_blocks);
     if (waves_for(longest) <= slots) {
-        int32_t best = INT32_MAX;
-        int32_t hi = std::max(longest, opt.split_blocks);
-        for (int32_t per_cu = 1; per_cu <= kDecodeWavesPerCu / kWavesPerGroup; ++per_cu) {
+        const int32_t shortest = std::min<int32_t>(kMinOneGenSplitBlocks, std::max(2, opt.split_blocks));
+        constexpr int32_t kMostPerCu = kDecodeWavesPerCu / kWavesPerGroup;
+        int64_t best = INT64_MAX / 10;
+        int32_t hi = longest;
+        if (waves_for(target_longest) > slots)
+            best = (int64_t)decode_cost(kMostPerCu, split, opt.light) * waves_for(split) / slots;
+        for (int32_t per_cu = 1; per_cu <= kMostPerCu; ++per_cu) {
             const int64_t most = (int64_t)per_cu * kWavesPerGroup * opt.num_cus;
             if (waves_for(hi) > most) continue;
-            int32_t lo = min_split;
+            int32_t lo = shortest;
             while (lo < hi) {
                 const int32_t mid = lo + (hi - lo) / 2;
                 if (waves_for(mid) <= most) hi = mid;
                 else lo = mid + 1;
             }
-            const int32_t cost = decode_cost(per_cu, hi, opt.light);
-            if (10 * (int64_t)cost < 9 * (int64_t)best) {
+            const int64_t cost = decode_cost(per_cu, hi, opt.light);
+            if (10 * cost < 9 * best) {
                 best = cost;
                 split = hi;
             }
+        }
+        // Rows that need no merge as they are, beside nothing else that does, are
+        // cut only where the steps saved are worth the merge kernel.
+        int32_t uncut = 0;
+        for (const Segment &s : segs) uncut = std::max(uncut, s.j1 - s.j0);
+        if (uncut > split && segs.size() == R.size() && !prefill_may_be_cut) {
+            const int64_t per_round = (int64_t)kWavesPerGroup * opt.num_cus;
+            const int32_t per_cu = (int32_t)((waves_for(uncut) + per_round - 1) / per_round);
+            if (decode_cost(per_cu, uncut, opt.light) <= best + kMergeCost) split = uncut;
         }
     }
 
@@ -260,9 +287,8 @@ int build_plan(const HostBatch &b, int32_t Hkv, int32_t Hq, int32_t D, const Pla
 
     // ---- prefill rows: tiles of consecutive tokens, all heads of a KV head
     plan.pdesc.clear();
-    const int32_t bt_tok = std::max(1, kPrefillQueries / G);
     plan.prefill_tokens_per_tile = bt_tok;
-    int64_t pf_work = 0, pf_tiles = 0;   // 64-key tiles summed over the prefill tiles
+    int64_t pf_work = 0;   // 64-key tiles summed over the prefill tiles
     for (int32_t r = 0; r < B; ++r) {
         if (b.kind[r] != ECHO_ROW_PREFILL) continue;
         const int32_t q = b.q_start[r + 1] - b.q_start[r];
@@ -280,7 +306,6 @@ int build_plan(const HostBatch &b, int32_t Hkv, int32_t Hq, int32_t D, const Pla
             d.next = 0;
             plan.pdesc.push_back(d);
             pf_work += (d.key_end + kPrefillTileKeys - 1) / kPrefillTileKeys;
-            ++pf_tiles;
         }
     }
     // More than two rounds at head_dim 64, where two workgroups share a CU: the

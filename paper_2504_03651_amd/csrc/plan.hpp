@@ -69,11 +69,8 @@ constexpr int kPrefillMinChainTiles = 2;  // fewest 64-key tiles moved to a chai
 // the bytes per block (a sweep of 16-128 blocks on the decode-only, mixed and
 // e4m3 batches).
 constexpr int64_t kSplitBytes = 384 * 1024;
-constexpr int kMinSplitBlocks = 6;        // shortest decode piece on small batches
-// Shortest piece that a device-built plan's regions are sized for: at 6 blocks
-// batches that fit the static entry point's scratch at 8 would outgrow it.  Pieces
-// are shorter where the batch's lengths leave room for them.
-constexpr int kMinRegionSplitBlocks = 8;
+constexpr int kMinSplitBlocks = 8;        // shortest decode piece on small batches
+constexpr int kMinOneGenSplitBlocks = 6;  // the same in a launch of one generation
 constexpr int kSplitTargetUnits = 2048;   // decode units below which pieces shrink
 #ifndef ECHO_EQ_GENS
 #define ECHO_EQ_GENS 3
@@ -110,6 +107,14 @@ constexpr int32_t decode_cost(int32_t per_cu, int32_t blocks, bool light) {
     constexpr int32_t step[2][3] = {{28, 43, 62}, {28, 30, 44}};
     return step[light ? 1 : 0][per_cu - 1] * ((blocks + 1) / 2);
 }
+
+// What a merge kernel that nothing else needs costs, on decode_cost's scale: about
+// 4 us.  8 rows of n blocks, left whole and cut at 6 blocks, on keys from HBM and
+// again on cached ones (GQA 32/8, head_dim 128, bf16): n = 8 13.5 and 13.4 us
+// (10.2 and 12.1 cached), n = 10 15.8 and 15.7 (11.4 and 13.6), n = 16 21.9 and
+// 16.1 (18.4 and 13.3); 64/8 at head_dim 64: n = 8 9.6 and 11.4, n = 12 12.0 and
+// 12.9, n = 16 14.3 and 12.9.  128 rows of 12 blocks 22.8 and 27.3 us.
+constexpr int32_t kMergeCost = 80;
 
 // Merge entries of a token from which its heads get a wave each: past 16 a
 // 16-lane group would walk them in several turns, a chain of loads each.
