@@ -177,6 +177,7 @@ struct Plan {
     std::vector<int32_t> tok_list, klim, merge_tok, merge_ptr, merge_ent;
     // scratch
     std::vector<int32_t> nro, rows, tail_start, seg_rows, cnt, moff, cursor, bucket, cuts, takers, ctail;
+    std::vector<double> seg_len, seg_slices;
     PlanLayout layout;
     PlanStats stats;
     int32_t waves_per_desc = 1;   // num_kv_heads * head_chunks

@@ -3,6 +3,7 @@ no partial results and no merge, where the launch fits one generation of waves
 as it is or the steps that a cut would save are fewer than a merge costs."""
 import ctypes
 
+import numpy as np
 import pytest
 
 from paper_2504_03651_amd import echo
@@ -45,3 +46,45 @@ def test_long_rows_are_cut_all_the_same():
     chunk = [W.RowSpec(W.PREFILL, 3000, 40)]
     st = _stats([W.RowSpec(W.DECODE, 127, 1)] * 8 + chunk, 32, 8, 128, W.KV_BF16)
     assert st.decode_items == 2 * 8 * 8
+
+
+def _rule(lens, wpd, light):
+    """Longest piece of unshared rows of `lens` blocks in one generation of waves
+    (12 per CU x 256 CUs), by trying every length; None past one generation."""
+    step = ((28, 43, 62), (28, 30, 44))[light]
+    default = 96 if light else 48
+    units = sum(lens) * wpd // 2048
+    target = max(8, min(default, units))
+    longest = max(target, min(4 * default, units))
+    waves = lambda sp: sum(-(-n // sp) for n in lens) * wpd  # noqa: E731
+    if waves(longest) > 3072:
+        return None
+    best, split = 1 << 62, target
+    for per_cu in (1, 2, 3):
+        fit = [sp for sp in range(6, max(longest, default) + 1) if waves(sp) <= 1024 * per_cu]
+        if fit and 10 * step[per_cu - 1] * ((fit[0] + 1) // 2) < 9 * best:
+            best, split = step[per_cu - 1] * ((fit[0] + 1) // 2), fit[0]
+    whole = max(lens)
+    if whole > split and step[-(-waves(whole) // 1024) - 1] * ((whole + 1) // 2) <= best + 80:
+        split = whole
+    return max(-(-n // -(-n // split)) for n in lens)
+
+
+@pytest.mark.parametrize("hq,hkv,d,kv", [(32, 8, 128, W.KV_BF16), (4, 4, 128, W.KV_BF16),
+                                         (32, 32, 128, W.KV_BF16), (32, 8, 128, W.KV_FP8)])
+def test_pieces_are_the_shortest_that_fit(hq, hkv, d, kv):
+    rng, checked = np.random.default_rng(5), 0
+    for n in (1, 2, 3, 5, 8, 17, 40, 64, 100, 250):
+        for top in (3, 9, 20, 60, 200):
+            lens = rng.integers(1, top + 1, n).tolist()
+            want = _rule(lens, hkv, kv != W.KV_BF16)
+            if want is None:
+                continue
+            w = W.build("rule", [W.RowSpec(W.DECODE, 16 * k - 1, 1) for k in lens], {}, hq, hkv, d,
+                        kv_dtype=kv, seed=3, values=False)
+            cp, cb, _keep = echo.host_structs(w)
+            lay, words = echo.plan_pack(cp, cb, hq)
+            p = words[lay["off_desc"]:lay["off_desc"] + 8 * lay["n_desc"]].reshape(-1, 8)
+            assert ((p[:, 4] - p[:, 3] + 15) // 16).max() == want, (n, top)
+            checked += 1
+    assert checked > 25
