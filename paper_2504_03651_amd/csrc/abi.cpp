@@ -368,7 +368,8 @@ struct AttnLaunch {
     int64_t n_desc = 0, n_merge_rows = 0, n_merge_wide = 0;
     int32_t n_pdesc_grid = 0;     // prefill descriptors that get workgroups (a capacity with counts)
     int32_t head_chunks = 1, heads_per_chunk = 1, waves_per_desc = 1, run_log2 = 0,
-            pf_max_blocks = 0, num_cus = 256;
+            pf_max_blocks = 0;
+    bool pf_dense = false;        // two prefill workgroups per CU
     // The decode kernel reads its part of the plan where the host packed it and
     // copies copy_words of it to the workspace for the kernels after it: it then
     // goes first, and no upload kernel before it
@@ -445,6 +446,7 @@ int launch_attention(const echo_kv_pool_t *pool, const echo_batch_t *batch, cons
     pf.scale_log2 = a.scale_log2;
     pf.out = out;
     pf.max_blocks = w.pf_max_blocks;
+    pf.dense = w.pf_dense;
     pf.head_chunks = w.head_chunks;
     pf.heads_per_chunk = w.heads_per_chunk;
     pf.part_o = a.part_o;
@@ -458,8 +460,7 @@ int launch_attention(const echo_kv_pool_t *pool, const echo_batch_t *batch, cons
     auto prefill = [&]() -> int {
         if (pf.n_logical <= 0) return ECHO_OK;
         if (ev && (e = hipEventRecord(ev[2], s)) != hipSuccess) return hip_fail(e, "hipEventRecord");
-        if ((e = launch_prefill(pf, D, fp8, w.num_cus, s)) != hipSuccess)
-            return hip_fail(e, "prefill launch");
+        if ((e = launch_prefill(pf, D, fp8, s)) != hipSuccess) return hip_fail(e, "prefill launch");
         if (ev && (e = hipEventRecord(ev[3], s)) != hipSuccess) return hip_fail(e, "hipEventRecord");
         return ECHO_OK;
     };
@@ -553,7 +554,10 @@ int attn_device_planned(const echo_kv_pool_t *pool, const echo_batch_t *batch, c
     a.waves_per_desc = L.waves_per_desc;
     a.run_log2 = 0;
     a.pf_max_blocks = L.pf_max_blocks;
-    a.num_cus = plan_options(pool).num_cus;
+    a.pf_dense = prefill_two_per_cu(
+        pool->head_dim,
+        prefill_tiles_at_least(batch->num_tokens, batch->num_rows, L.tile_tokens) * pool->num_kv_heads,
+        L.pf_max_blocks, plan_options(pool).num_cus);
     return launch_attention(pool, batch, q, num_q_heads, sm_scale, out, a, s, ev);
 }
 
@@ -630,7 +634,7 @@ int attn_planned(const echo_kv_pool_t *pool, const echo_batch_t *batch, const vo
     a.waves_per_desc = plan.waves_per_desc;
     a.run_log2 = run_log2_for(plan.sibling_waves);
     a.pf_max_blocks = pf_blocks;
-    a.num_cus = plan_options(pool).num_cus;
+    a.pf_dense = plan.prefill_dense;
     return launch_attention(pool, batch, q, num_q_heads, sm_scale, out, a, s, ev);
 }
 

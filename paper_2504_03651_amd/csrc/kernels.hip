@@ -1842,13 +1842,11 @@ static hipError_t launch_prefill_t(const PrefillArgs &p, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_prefill(const PrefillArgs &p, int head_dim, bool fp8, int num_cus, hipStream_t s) {
+static_assert(2 * (PfLds<64>::BYTES + 4 * kTwoPerCuMaxBlocks) <= kPfLdsLimit, "two workgroups per CU");
+
+hipError_t launch_prefill(const PrefillArgs &p, int head_dim, bool fp8, hipStream_t s) {
     if (p.n_logical <= 0) return hipSuccess;
-    // Two workgroups per CU pay past two rounds of CUs.  Measured (pipelined ->
-    // DENSE) at 272 and 312 workgroups 47.6 -> 53.3 and 54.7 -> 61.2 us, at 512
-    // 56.2 -> 57.2 and 95.0 -> 93.2, at 640 146.3 -> 125.7 and 38.7 -> 35.2, at
-    // 1,024 261 -> 221 and 54.0 -> 44.5.
-    if (head_dim == 64 && p.n_logical > 2 * (int64_t)num_cus)
+    if (p.dense)
         return fp8 ? launch_prefill_t<64, true, true>(p, s) : launch_prefill_t<64, false, true>(p, s);
     if (head_dim == 64 && !fp8) return launch_prefill_t<64, false>(p, s);
     if (head_dim == 64) return launch_prefill_t<64, true>(p, s);

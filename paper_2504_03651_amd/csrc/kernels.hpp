@@ -69,6 +69,7 @@ struct PrefillArgs {
     float scale_log2;
     float *out;
     int32_t max_blocks;             // most blocks any piece reads (ids staged in LDS)
+    bool dense;                     // two workgroups per CU (head_dim 64, no chained descriptors)
     int32_t head_chunks, heads_per_chunk;   // partial-slot layout shared with decode
     float *part_o, *part_lse;       // partial results of pieces of split key ranges
 };
@@ -136,7 +137,7 @@ int prefill_max_blocks(int head_dim);
 // Attention launchers; each returns hipSuccess without launching when it
 // has no work.  The merge reads the partial results of both others, so it
 // runs after them.
-hipError_t launch_prefill(const PrefillArgs &p, int head_dim, bool fp8, int num_cus, hipStream_t s);
+hipError_t launch_prefill(const PrefillArgs &p, int head_dim, bool fp8, hipStream_t s);
 hipError_t launch_decode(const AttnArgs &a, int head_dim, bool fp8, hipStream_t s);
 hipError_t launch_merge(const MergeArgs &m, int head_dim, hipStream_t s);
 

@@ -311,6 +311,7 @@ int build_plan(const HostBatch &b, int32_t Hkv, int32_t Hq, int32_t D, const Pla
     plan.pdesc.clear();
     plan.prefill_tokens_per_tile = bt_tok;
     int64_t pf_work = 0;   // 64-key tiles summed over the prefill tiles
+    int32_t pf_keys = 0;   // most keys of one
     for (int32_t r = 0; r < B; ++r) {
         if (b.kind[r] != ECHO_ROW_PREFILL) continue;
         const int32_t q = b.q_start[r + 1] - b.q_start[r];
@@ -328,16 +329,18 @@ int build_plan(const HostBatch &b, int32_t Hkv, int32_t Hq, int32_t D, const Pla
             d.next = 0;
             plan.pdesc.push_back(d);
             pf_work += (d.key_end + kPrefillTileKeys - 1) / kPrefillTileKeys;
+            pf_keys = std::max(pf_keys, d.key_end);
         }
     }
-    // More than two rounds at head_dim 64, where two workgroups share a CU: the
-    // longest key ranges first over all rows, so that the launch does not end
-    // on a long tile (12 prompts: 142 -> 130 us).  By quarters of a power of
-    // two, so that the tiles of rows of about one length stay together and
-    // share their keys in L2.  At head_dim 128, one workgroup per CU, the order
-    // by rows is the better one (12 prompts 139 us against 141; four rows of
-    // 32,768 keys sorted by exact length 4% slower).
-    if (D == 64 && pf_tiles * Hkv > 2 * (int64_t)opt.num_cus)
+    // Where two workgroups share a CU, the longest key ranges first over all rows,
+    // so that the launch does not end on a long tile (12 prompts: 142 -> 130 us).
+    // By quarters of a power of two, so that the tiles of rows of about one length
+    // stay together and share their keys in L2.  At head_dim 128, one workgroup
+    // per CU, the order by rows is the better one (12 prompts 139 us against 141;
+    // four rows of 32,768 keys sorted by exact length 4% slower).
+    plan.prefill_dense =
+        prefill_two_per_cu(D, pf_tiles * Hkv, (pf_keys + kBlock - 1) / kBlock, opt.num_cus);
+    if (plan.prefill_dense)
         std::stable_sort(plan.pdesc.begin(), plan.pdesc.end(),
                          [](const PrefillDesc &x, const PrefillDesc &y) {
                              return length_class(x.key_end) > length_class(y.key_end);

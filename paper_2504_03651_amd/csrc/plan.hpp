@@ -64,6 +64,23 @@ static_assert(sizeof(PrefillDesc) == 32, "prefill descriptor layout");
 constexpr int kPrefillTileKeys = 64;      // keys per LDS tile of the prefill kernel
 constexpr int kPrefillMinPieceTiles = 8;  // shortest piece a long key range is cut into
 constexpr int kPrefillMinChainTiles = 2;  // fewest 64-key tiles moved to a chained piece
+
+// Two prefill workgroups per CU (head_dim 64): past two rounds of CUs, and while
+// two fit the LDS (a workgroup stages its row's block ids).  Measured (one per CU
+// -> two) at 272 and 312 workgroups 47.6 -> 53.3 and 54.7 -> 61.2 us, at 512 56.2 ->
+// 57.2 and 95.0 -> 93.2, at 640 146.3 -> 125.7 and 38.7 -> 35.2, at 1,024 261 -> 221
+// and 54.0 -> 44.5.
+constexpr int kTwoPerCuMaxBlocks = 8000;
+constexpr bool prefill_two_per_cu(int head_dim, int64_t workgroups, int64_t max_blocks, int num_cus) {
+    return head_dim == 64 && workgroups > 2 * (int64_t)num_cus && max_blocks <= kTwoPerCuMaxBlocks;
+}
+// Prefill tiles that have work at least in a device-built plan, per KV head: its
+// descriptor region has a spare tile per row, which decode rows never fill.  Every
+// row has a token; the others are the chunks'.
+constexpr int64_t prefill_tiles_at_least(int64_t num_tokens, int64_t num_rows, int64_t tile_tokens) {
+    return num_tokens > num_rows ? (num_tokens - num_rows) / tile_tokens : 0;
+}
+
 // Decode key ranges are cut into pieces of about kSplitBytes of K+V per KV
 // head: 48 blocks of bf16 at head_dim 128, 96 of e4m3, whose waves move half
 // the bytes per block (a sweep of 16-128 blocks on the decode-only, mixed and
@@ -174,6 +191,7 @@ struct Plan {
     int32_t pdesc_grid = 0;       // leading descriptors of pdesc that get workgroups
     std::vector<int32_t> bounds;
     int32_t prefill_tokens_per_tile = 1;
+    bool prefill_dense = false;   // two prefill workgroups per CU (prefill_two_per_cu)
     std::vector<int32_t> tok_list, klim, merge_tok, merge_ptr, merge_ent;
     // scratch
     std::vector<int32_t> nro, rows, tail_start, seg_rows, cnt, moff, cursor, bucket, cuts, takers, ctail;
