@@ -870,9 +870,16 @@ __device__ __forceinline__ void prefill_piece(const PrefillArgs &a, int kvh, int
 #pragma unroll
         for (int i = 0; i < NT; ++i) acc[nn][i] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
     float m_run[2] = {-INFINITY, -INFINITY};
-    // derived from m_run, refreshed when it moves: the exponent offset
-    // (-m_run, 0 while m_run is -inf) and the two lazy-rescale thresholds
-    float m_neg[2] = {0.f, 0.f}, m_hig[2] = {-INFINITY, -INFINITY}, m_hi8[2] = {-INFINITY, -INFINITY};
+    // derived from m_run: the exponent offset (-m_run, 0 while m_run is -inf)
+    // and the two lazy-rescale thresholds; kept and refreshed when m_run moves, or
+    // for DENSE, whose registers are short, taken from it at each use
+    float neg_at[2] = {0.f, 0.f}, hig_at[2] = {-INFINITY, -INFINITY}, hi8_at[2] = {-INFINITY, -INFINITY};
+    auto m_neg = [&](int nn) -> float {
+        if constexpr (DENSE) return m_run[nn] == -INFINITY ? 0.f : -m_run[nn];
+        else return neg_at[nn];
+    };
+    auto m_hig = [&](int nn) -> float { return DENSE ? m_run[nn] + kGuard : hig_at[nn]; };
+    auto m_hi8 = [&](int nn) -> float { return DENSE ? m_run[nn] + 8.f : hi8_at[nn]; };
     // The softmax denominator is a P.V product with V = 1 (every row of
     // lacc[nn] holds the column sum), so it sums exactly the rounded weights
     // that P.V uses and costs one MFMA per chunk instead of 16 adds per lane
@@ -1046,9 +1053,11 @@ __device__ __forceinline__ void prefill_piece(const PrefillArgs &a, int kvh, int
 #pragma unroll
             for (int i = 0; i < NT; ++i) acc[nn][i] *= alpha;
             m_run[nn] = mnew[nn];
-            m_neg[nn] = mnew[nn] == -INFINITY ? 0.f : -mnew[nn];
-            m_hig[nn] = mnew[nn] + kGuard;
-            m_hi8[nn] = mnew[nn] + 8.f;
+            if constexpr (!DENSE) {
+                neg_at[nn] = mnew[nn] == -INFINITY ? 0.f : -mnew[nn];
+                hig_at[nn] = mnew[nn] + kGuard;
+                hi8_at[nn] = mnew[nn] + 8.f;
+            }
         }
     };
     // exponentials of one chunk against m_run, packed to bf16 (fp16 for e4m3)
@@ -1059,7 +1068,7 @@ __device__ __forceinline__ void prefill_piece(const PrefillArgs &a, int kvh, int
             for (int t = 0; t < 2; ++t)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const float pe = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[t][nn][r], f, m_neg[nn]));
+                    const float pe = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[t][nn][r], f, m_neg(nn)));
                     pf[nn][4 * t + r] = (PE)pe;
                 }
         }
@@ -1085,7 +1094,7 @@ __device__ __forceinline__ void prefill_piece(const PrefillArgs &a, int kvh, int
         PT p0[2], p1[2];
         qk(kl, 0, s0);
         prep(buf, kt, 0, masked, s0, m0, f0);
-        if (__any(m0[0] > m_hig[0] || m0[1] > m_hig[1])) {
+        if (__any(m0[0] > m_hig(0) || m0[1] > m_hig(1))) {
             const float mn[2] = {fmaxf(m_run[0], wave_max_xor16_32(m0[0])),
                                  fmaxf(m_run[1], wave_max_xor16_32(m0[1]))};
             rescale(mn);
@@ -1093,7 +1102,7 @@ __device__ __forceinline__ void prefill_piece(const PrefillArgs &a, int kvh, int
         qk(kl, 1, s1);          // MFMA ...
         expo(s0, p0, f0);       // ... with the exponentials of chunk 0
         prep(buf, kt, 1, masked, s1, m1, f1);
-        if (__any(m1[0] > m_hig[0] || m1[1] > m_hig[1])) {
+        if (__any(m1[0] > m_hig(0) || m1[1] > m_hig(1))) {
             // chunk 0's probabilities, not yet added, move with the reference
             const float mn[2] = {fmaxf(m_run[0], wave_max_xor16_32(m1[0])),
                                  fmaxf(m_run[1], wave_max_xor16_32(m1[1]))};
@@ -1110,10 +1119,10 @@ __device__ __forceinline__ void prefill_piece(const PrefillArgs &a, int kvh, int
         expo(s1, p1, f1);       // ... with the exponentials of chunk 1
         pv(vl, 1, p1);
         const float mt[2] = {vmax(m0[0], m1[0]), vmax(m0[1], m1[1])};
-        if (__any(mt[0] > m_hi8[0] || mt[1] > m_hi8[1])) {
+        if (__any(mt[0] > m_hi8(0) || mt[1] > m_hi8(1))) {
             const float mc[2] = {wave_max_xor16_32(mt[0]), wave_max_xor16_32(mt[1])};
-            const float mn[2] = {mc[0] > m_hi8[0] ? mc[0] : m_run[0],
-                                 mc[1] > m_hi8[1] ? mc[1] : m_run[1]};
+            const float mn[2] = {mc[0] > m_hi8(0) ? mc[0] : m_run[0],
+                                 mc[1] > m_hi8(1) ? mc[1] : m_run[1]};
             rescale(mn);
         }
     };
@@ -1131,7 +1140,7 @@ __device__ __forceinline__ void prefill_piece(const PrefillArgs &a, int kvh, int
             PT pr[2];
             qk(kl, ch, sc);
             prep(buf, kt, ch, masked, sc, m, f);
-            if (__any(m[0] > m_hig[0] || m[1] > m_hig[1])) {
+            if (__any(m[0] > m_hig(0) || m[1] > m_hig(1))) {
                 const float mn[2] = {fmaxf(m_run[0], wave_max_xor16_32(m[0])),
                                      fmaxf(m_run[1], wave_max_xor16_32(m[1]))};
                 rescale(mn);
@@ -1141,10 +1150,10 @@ __device__ __forceinline__ void prefill_piece(const PrefillArgs &a, int kvh, int
             mt[0] = vmax(mt[0], m[0]);
             mt[1] = vmax(mt[1], m[1]);
         }
-        if (__any(mt[0] > m_hi8[0] || mt[1] > m_hi8[1])) {
+        if (__any(mt[0] > m_hi8(0) || mt[1] > m_hi8(1))) {
             const float mc[2] = {wave_max_xor16_32(mt[0]), wave_max_xor16_32(mt[1])};
-            const float mn[2] = {mc[0] > m_hi8[0] ? mc[0] : m_run[0],
-                                 mc[1] > m_hi8[1] ? mc[1] : m_run[1]};
+            const float mn[2] = {mc[0] > m_hi8(0) ? mc[0] : m_run[0],
+                                 mc[1] > m_hi8(1) ? mc[1] : m_run[1]};
             rescale(mn);
         }
     };
@@ -1247,6 +1256,7 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs &a, int P) {
     if (a.counts && di >= ro_load(a.counts, kHdrPdesc)) return;
     for (;;) {
         prefill_piece<D, FP8, DENSE>(a, kvh, di);
+        if constexpr (DENSE) break;   // no chains there, and their loop costs registers
         const int next = __builtin_amdgcn_readfirstlane(((const int32_t *)(a.pdesc + di))[7]);
         if (next <= 0) break;
         __syncthreads();   // the next descriptor refills the LDS ring and block ids
@@ -1254,13 +1264,16 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs &a, int P) {
     }
 }
 
-// One workgroup per CU at head_dim 128 (222-246 VGPRs).  At head_dim 64 half
-// the products meet the same softmax work, and the waves of one workgroup,
-// which a barrier per tile keeps in step, leave the matrix cores idle; DENSE
-// holds a wave to 128 VGPRs so that two workgroups share a CU, and overlaps one
-// workgroup's softmax with the other's products instead of pipelining the two
-// chunks of a tile.  12 prompts of 84-1,428 tokens (GQA 64/8), 0.52 -> 0.62
-// PFLOP/s: 168 -> 142 us, and 130 us with the longest tiles first.
+// One workgroup per CU at head_dim 128 (232 VGPRs, e4m3 246).  At head_dim 64
+// half the products meet the same softmax work, and the waves of one workgroup,
+// which a barrier per tile keeps in step, leave the matrix cores idle; DENSE holds
+// a wave to 128 VGPRs, without spilling, so that two workgroups share a CU, and
+// overlaps one workgroup's softmax with the other's products instead of pipelining
+// the two chunks of a tile.  Chained descriptors, which only launches of at most
+// one round have, are left to the other form: the loop over them holds addresses
+// in registers.  12 prompts of 84-1,428 tokens (GQA 64/8), the whole call: 157 ->
+// 131 us, e4m3 171 -> 138 (with 6 and 15 registers spilled 138 and 152); the
+// kernel, averaged under a trace, 138 and 148 us.
 template <int D, bool FP8, bool DENSE>
 __global__ __launch_bounds__(kPfThreads, DENSE ? 4 : 1) void prefill_kernel(PrefillArgs a) {
     prefill_body<D, FP8, DENSE>(a, blockIdx.x);

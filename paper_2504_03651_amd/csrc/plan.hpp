@@ -66,10 +66,13 @@ constexpr int kPrefillMinPieceTiles = 8;  // shortest piece a long key range is 
 constexpr int kPrefillMinChainTiles = 2;  // fewest 64-key tiles moved to a chained piece
 
 // Two prefill workgroups per CU (head_dim 64): past two rounds of CUs, and while
-// two fit the LDS (a workgroup stages its row's block ids).  Measured (one per CU
-// -> two) at 272 and 312 workgroups 47.6 -> 53.3 and 54.7 -> 61.2 us, at 512 56.2 ->
-// 57.2 and 95.0 -> 93.2, at 640 146.3 -> 125.7 and 38.7 -> 35.2, at 1,024 261 -> 221
-// and 54.0 -> 44.5.
+// two fit the LDS (a workgroup stages its row's block ids).  Measured, one per CU
+// -> two, on 0, 500 and 2,000 cached keys, the whole call: 64/8 heads at 528
+// workgroups 24.9 -> 22.5, 56.2 -> 48.1 and 137 -> 121 us (e4m3 26.5 -> 22.5, 59.8 ->
+// 52.0, 151 -> 137), at 1,040 36.7 -> 33.2, 86.6 -> 71.4 and 237 -> 203 (39.4 -> 32.7,
+// 93.7 -> 76.1, 249 -> 213); 16/16 heads at 528 59.0 -> 56.8, 79.1 -> 74.2 and 156 ->
+// 143 (64.4 -> 62.1, 86.9 -> 81.8, 171 -> 160).  Below two rounds it is mixed: 16/16
+// at 400 46.8 -> 51.4, 66.8 -> 68.2 and 126 -> 117.
 constexpr int kTwoPerCuMaxBlocks = 8000;
 constexpr bool prefill_two_per_cu(int head_dim, int64_t workgroups, int64_t max_blocks, int num_cus) {
     return head_dim == 64 && workgroups > 2 * (int64_t)num_cus && max_blocks <= kTwoPerCuMaxBlocks;
