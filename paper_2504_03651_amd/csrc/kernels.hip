@@ -1658,7 +1658,7 @@ __global__ __launch_bounds__(kPlanThreads) void dev_plan_kernel(DevPlanArgs a) {
         const bool merged = np > 1;
         PlanCount tot;
         const PlanCount at = plan_scan({np, merged ? 1 : 0, merged ? np : 0, tiles}, live, wsum, tot);
-        const bool fits = done_pf + at.pf + tiles <= a.cap_pdesc;
+        const bool fits = tiles == 0 || done_pf + at.pf + tiles <= a.cap_pdesc;
         row_dec[tid] = at.dec;
         row_pf[tid] = (int32_t)min<int64_t>(at.pf, a.cap_pdesc - min<int64_t>(done_pf, a.cap_pdesc));
         row_np[tid] = np;

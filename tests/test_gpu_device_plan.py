@@ -53,3 +53,31 @@ def test_device_plan_edges(name, kv):
     err, _ = attn_error(it.out.cpu().numpy().reshape(ref.shape), ref)
     say(f"       max abs err {err:.3e}")
     assert err <= ATOL
+
+
+def test_only_the_rows_that_get_no_work_are_counted_as_skipped():
+    # max_q_len 1 leaves no room for prefill tiles: the row of four tokens is
+    # skipped, and the decode rows after it are computed and not counted
+    import torch
+    from paper_2504_03651_amd.session import Iteration
+    rows = [W.RowSpec(W.DECODE, 300, 1), W.RowSpec(W.PREFILL, 20, 4)] + \
+           [W.RowSpec(W.DECODE, c, 1) for c in (500, 40, 900)]
+    w = W.build("skipped", rows, {}, 4, 2, 64, seed=67)
+    say("[case] device plan, a row that does not fit")
+    it = Iteration(w, mirrors=False)
+    it.copy()
+    it.append()
+    it.batch.max_q_len = 1
+    it.out.fill_(7.0)
+    it.attend()
+    torch.cuda.synchronize()
+    hdr = it.workspace[:64 * 4].view(torch.int32).cpu().numpy()
+    assert hdr[4] == 1
+    _, ref = oracle.run_iteration(w)
+    got = it.out.cpu().numpy()
+    ref = ref.reshape(got.shape)
+    assert (got[1:5] == 7.0).all()
+    keep = [0, 5, 6, 7]
+    err, _ = attn_error(got[keep], ref[keep])
+    say(f"       max abs err {err:.3e}")
+    assert err <= ATOL
