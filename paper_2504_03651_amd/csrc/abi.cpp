@@ -722,7 +722,9 @@ int echo_kv_append(const echo_kv_pool_t *pool, const echo_batch_t *batch, const 
     const int64_t bpr =
         std::min<int64_t>((batch->max_q_len + kBlock - 2) / kBlock + 1, batch->max_blocks_per_row);
     const int64_t padded = (int64_t)batch->num_rows * bpr * pool->num_kv_heads;
-    a.blocks_per_row = padded <= 2 * a.n_units && padded >> 32 == 0 ? (int32_t)bpr : 0;
+    // (and its grid, four units a workgroup of 256, is one of fewer than 2^32 threads)
+    a.blocks_per_row =
+        padded <= 2 * a.n_units && (padded + 3) / 4 < (int64_t)1 << 24 ? (int32_t)bpr : 0;
     hipError_t e = launch_append(a, pool->head_dim, pool->dtype == ECHO_KV_FP8_E4M3,
                                  (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "append launch");
