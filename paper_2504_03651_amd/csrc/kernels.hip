@@ -56,7 +56,8 @@ __device__ __forceinline__ bf16x8_t e4m3x8_to_bf16x8(u32x2_t w) {
 
 // Two fp32 -> two OCP e4m3fn codes in the low 16 bits, round to nearest even,
 // saturating to +-448, NaN to 0x7F: gfx950's v_cvt_pk_fp8_f32 on the clamped
-// values (checked on all 2^32 floats against an integer encoder).
+// values (the tests compare the codes of every bf16 value, at scales inside and
+// outside the quotient's fast range, with the oracle's encoder).
 __device__ __forceinline__ uint32_t f32x2_to_e4m3(float x, float y) {
     const uint32_t w = (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(
         __builtin_amdgcn_fmed3f(x, -448.f, 448.f), __builtin_amdgcn_fmed3f(y, -448.f, 448.f), 0, false);
