@@ -1,8 +1,8 @@
 """The append's e4m3 codes for every bf16 value (infinities, NaN, zeros of both
 signs, subnormals and all rounding ties among them), bit for bit against the
 oracle's encoder, at scales that the rounded quotient is taken by its reciprocal
-for and at ones that it is divided for: whole blocks, blocks written in part and
-single slots, each with scales that stand in the pool."""
+for and at ones that it is divided for: blocks written in part and single slots,
+whose scales stand in the pool."""
 import numpy as np
 import pytest
 

@@ -2,8 +2,10 @@
 one generation of waves reads it in pinned host memory and copies it for the
 kernels after it; larger launches, and those beside a large prefill, copy it
 first.  Both sides of that rule (3,072 waves, 512 prefill workgroups on 256
-CUs), with and without chunks and merges, against the oracle; and a captured
-call replayed with other work in between, against the eager result."""
+CUs), with and without chunks and merges, against the oracle; batches of different
+plans through one buffer and through the ring, with nothing waited for in between;
+and a captured call replayed with other work in between, against the eager
+result."""
 import ctypes
 
 import pytest
@@ -44,6 +46,43 @@ def test_plan_delivery(name):
     err, _ = attn_error(it.out.cpu().numpy().reshape(ref.shape), ref)
     say(f"       max abs err {err:.3e}")
     assert err <= ATOL
+
+
+@pytest.mark.parametrize("slots", [1, 4])
+def test_plans_that_follow_each_other(slots):
+    # a buffer is rewritten with the next plan as soon as it is handed out again:
+    # a kernel that read another call's plan would give that call's rows
+    import torch
+    from paper_2504_03651_amd import echo
+    from paper_2504_03651_amd.session import Iteration
+    order = ["direct-merge", "copied", "direct", "chunk-only", "copied-chunk", "direct-chunk",
+             "direct-two-rounds", "copied-past-them"]
+    its, refs = [], []
+    for k, name in enumerate(order):
+        rows = CASES[name][k % 2:] + CASES[name][:k % 2]    # in another order
+        w = W.build(name, rows, {}, 32, 32, 64, seed=107 + k)
+        it = Iteration(w)
+        it.copy()
+        it.append()
+        its.append(it)
+        refs.append(oracle.run_iteration(w)[1])
+    # one workspace for all calls of the stream, sized for the largest
+    ws = torch.empty(max(it.workspace.numel() for it in its), dtype=torch.uint8, device="cuda")
+    hw = echo.HostWorkspace(slots=slots)
+    outs = []
+    torch.cuda.synchronize()
+    say(f"[case] plans one after the other, {slots} buffers")
+    for turn in range(3):
+        for k in range(len(its)):
+            it = its[(5 * k + turn) % len(its)]
+            out = torch.full_like(it.out, float("nan"))
+            echo.attn_mixed(it.pool, it.batch, it.q, 32, it.w.sm_scale, out, ws, host_workspace=hw)
+            outs.append(((5 * k + turn) % len(its), out))
+    torch.cuda.synchronize()
+    for i, out in outs:
+        err, _ = attn_error(out.cpu().numpy().reshape(refs[i].shape), refs[i])
+        assert err <= ATOL, (order[i], err)
+    hw.close()
 
 
 @pytest.mark.parametrize("name", ["direct-merge", "copied-chunk"])
