@@ -303,8 +303,9 @@ int check_host_workspace(void *host_ws, size_t bytes, size_t need, void **dev_pt
 
 // Scalar bounds of the device-built plan for a batch without host mirrors.
 struct DevLayout {
-    int32_t split_blocks = 0, min_split = 0, max_split = 0, wave_slots = 0, tile_tokens = 0, slots_per_desc = 0, head_chunks = 1,
-            heads_per_chunk = 1, waves_per_desc = 1, pf_max_blocks = 0;
+    int32_t split_blocks = 0, min_split = 0, max_split = 0, wave_slots = 0, tile_tokens = 0,
+            slots_per_desc = 0, head_chunks = 1, heads_per_chunk = 1, waves_per_desc = 1,
+            pf_max_blocks = 0;
     int64_t cap_desc = 0, cap_pdesc = 0, cap_mrows = 0, cap_ent = 0, cap_slots = 0;
     int64_t off_row_info = 0, off_desc = 0, off_pdesc = 0, off_mtok = 0, off_mptr = 0,
             off_ment = 0, off_lse = 0, off_o = 0, total_words = 0;
@@ -590,12 +591,14 @@ int attn_planned(const echo_kv_pool_t *pool, const echo_batch_t *batch, const vo
     pack_plan(plan, host_workspace);
     hipError_t e;
     // A decode launch of one generation reads its descriptors over the host
-    // link, which every wave waits for once (1.4 us), instead of waiting for a
-    // copy kernel (3.3 us and the gap after it): 8 rows 33.4 -> 30.8 us a call
-    // and append.  Launches of several generations would wait in each.  Nor
-    // where the prefill takes more than two rounds of CUs and 3 us are nothing:
-    // the decode kernel is better off behind it (28 rows of 32,768 keys shared
-    // with four chunks: 434 us first, 367 us behind; the pass 0.6-1.1% slower).
+    // link, which every wave waits for once, instead of waiting for a copy kernel
+    // and the gap after it: 2.5-3 us less a call from 128 to 3,072 waves of 2-48
+    // blocks, all layouts (32 waves: 3 us less to the same).  The kernel itself gets
+    // longer by that wait (8 rows, 18 us under a trace).  Launches of several
+    // generations would wait in each.  Nor where the prefill takes more than two
+    // rounds of CUs and 3 us are nothing: the decode kernel is better off behind it
+    // (28 rows of 32,768 keys shared with four chunks: 434 us first, 367 us behind;
+    // the pass 0.6-1.1% slower).
     const int32_t num_cus = plan_options(pool).num_cus;
     const bool direct =
         L.n_desc > 0 && L.n_desc * plan.waves_per_desc <= (int64_t)kDecodeWavesPerCu * num_cus &&

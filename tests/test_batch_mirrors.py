@@ -1,5 +1,7 @@
-"""The addresses a DeviceBatch passes for its host mirrors follow the arrays:
-also after a mirror was replaced, and in a copy of the batch (CPU)."""
+"""Host state that calls keep or check (CPU): the addresses a DeviceBatch passes
+for its host mirrors follow the arrays, also after a mirror was replaced and in a
+copy of the batch; the block copy's check of its pairs; the ring of host buffers;
+the size of a device-built plan against the static entry point's scratch."""
 import copy
 import ctypes
 
